@@ -14,7 +14,8 @@
  *                   operands become one access, and only unaligned work stays
  *                   under a branch (the "Unpredication" subsection).
  *   MELD_AUTO       the library picks per stage (measured divergence and the
- *                   tuned plan).
+ *                   tuned plan). meld_sort_u32 then also picks the algorithm:
+ *                   the network for small arrays, radix passes above.
  *   MELD_MELDED_INPLACE  for the region: the melded form with the two sides'
  *                   gathers aligned too (one gather instruction per step,
  *                   address selected per lane). MELD_MELDED leaves those
@@ -30,9 +31,9 @@
  *     asynchronous on it; results are ready once the stream has reached the
  *     call. Kernel faults surface at the caller's next synchronisation.
  *     Exception: a call that needs more context scratch than the context
- *     holds (the first non-power-of-two sort at a larger padding, a
- *     segmented sort over more segments than before, the first MELD_AUTO
- *     trials of a shape) waits for the device (hipDeviceSynchronize) before it
+ *     holds (the first non-power-of-two sort at a larger padding, a larger
+ *     MELD_AUTO sort than before, a segmented sort over more segments than
+ *     before, the first MELD_AUTO trials of a shape) waits for the device (hipDeviceSynchronize) before it
  *     frees the smaller buffer and allocates the larger one; later calls of
  *     that size or less are asynchronous. meld_sort_u32_noalloc never
  *     allocates or waits.
@@ -128,6 +129,12 @@ const char *meld_last_error(void);
  * descending order otherwise, with strict compares. Positions n..N-1 hold
  * the value 0xFFFFFFFF (for pairs (0xFFFFFFFF, 0xFFFFFFFF)) in library
  * scratch; nothing past n is read or written in the caller's arrays.
+ * MELD_AUTO runs the network up to 2^15 keys or 2^17 pairs, with
+ * MELD_OPT_SORT_LOG_TILE or MELD_OPT_LANE_EXCHANGE set, under capture, and
+ * where the scratch below cannot be allocated; otherwise a least-significant-
+ * digit radix sort, which gives the same (unique) result in at most four
+ * passes per word. Its scratch, owned by the context, is as large as the
+ * arrays plus at most 1/8 of that for digit counts.
  *
  * keys:    device u32[n], sorted in place (unsigned order).
  * payload: NULL, or device u32[n] moved with its key. With a payload the
@@ -168,7 +175,8 @@ meld_status meld_sort_u32_noalloc(meld_ctx *ctx, uint32_t *keys, uint32_t *paylo
  * the last, and launch_ms[i] receives the time between events i and i+1 in
  * milliseconds (launch i of the plan meld_sort_plan_describe lists; for a
  * non-power-of-two n the first also holds the fill of the padding). Used to
- * measure each kernel against its roofline. Synchronous.
+ * measure each kernel of the network against its roofline: it always runs the
+ * network, for MELD_AUTO the tuned one. Synchronous.
  * launch_ms: host float[cap]; *n_launches receives the number of launches
  * (0 for n <= 1).
  * Errors: as meld_sort_u32, plus MELD_EINVAL for NULL launch_ms or
@@ -184,10 +192,12 @@ meld_status meld_sort_u32_timed(meld_ctx *ctx, uint32_t *keys, uint32_t *payload
 meld_status meld_sort_u32_steps(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size_t n,
                                 int64_t max_steps, meld_variant variant, void *stream);
 
-/* The launches meld_sort_u32 would enqueue for n elements (the network of
- * the Motivating Example section, Figure 1, split into on-chip and HBM
- * passes), as JSON in buf (NUL-terminated), without launching anything:
- *   {"n", "log_n", "pairs", "tuned", "log_tile", "low", "high",
+/* The launches of the network that meld_sort_u32_timed would enqueue for n
+ * elements (the network of the Motivating Example section, Figure 1, split
+ * into on-chip and HBM passes), as JSON in buf (NUL-terminated), without
+ * launching anything; "sorts_by" says whether meld_sort_u32 on this context
+ * runs this network or, under MELD_AUTO, radix passes ("network", "radix"):
+ *   {"n", "log_n", "pairs", "tuned", "sorts_by", "log_tile", "low", "high",
  *    "hbm_passes", "steps", "passes": [{"kind", "steps", "m", "b_hi", "b_lo"}]}
  * kind "tile" (everything in one tile), "local" (every tile's phases up to
  * the tile), "regs" / "gather" (steps j = 2^b_hi .. 2^b_lo of phase 2^m

@@ -112,6 +112,13 @@ constexpr uint32_t kMaxFusedSteps = 6;
 hipError_t launch_bitonic_global(const SortArray &a, uint32_t log_n, uint32_t m, uint32_t b_hi,
                                  uint32_t b_lo, int32_t step_limit, hipStream_t stream);
 
+// Radix sort of keys[0..n) (with vals, of the (key, value) pairs in
+// lexicographic order), n < 2^31 (radix.hip). scratch: radix_scratch_words
+// u32, 16-byte aligned. The arrays may have any 4-byte alignment.
+size_t radix_scratch_words(uint32_t n, bool pairs);
+hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t n, uint32_t *scratch,
+                             hipStream_t stream);
+
 hipError_t launch_fill_u32(uint32_t *p, uint32_t value, size_t count, hipStream_t stream);
 
 // Seeded inputs generated on the device (gen.hip).

@@ -709,6 +709,20 @@ SortPlan fixed_plan(const meld_ctx *ctx, bool pairs, size_t n, meld_variant v) {
     return SortPlan{plan_log_tile(ctx, pairs, log2_ceil(n)), m, m, plan_xch(ctx)};
 }
 
+// Whether MELD_AUTO sorts n elements by the radix passes (radix.hip) rather
+// than by the network: above the sizes where their launches cost as much as
+// the network's (one MI355X, radix against the tuned network, microseconds:
+// keys 2^15 35 / 33, 49153 38 / 48, 2^16 38 / 42; pairs with their index
+// 49153 55 / 75, 2^17 63 / 74; pairs with random payloads, twice the passes,
+// 2^17 86 / 74, 196609 89 / 117). An option that fixes how the network runs
+// asks for the network. Not under capture: the recorded launches would hold
+// the address of scratch that a later call of the context may replace, where
+// the network of a power of two has none.
+bool radix_sorts(const meld_ctx *ctx, bool pairs, size_t n) {
+    return ctx->sort_log_tile == 0 && ctx->lane_exchange < 0 &&
+           n > (pairs ? (size_t)1 << 17 : (size_t)1 << 15);
+}
+
 // Probe of one tile's network: mixed-wave fraction of the phases k <= 64 and
 // k >= 128.
 meld_status probe_network(meld_ctx *ctx, uint32_t log_t, hipStream_t s, double *mixed_lo,
@@ -1273,6 +1287,17 @@ meld_status meld_sort_u32(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size
         return fail(MELD_EINVAL, "meld_sort_u32: payload is not a device pointer on device %d",
                     ctx->device);
     const hipStream_t s = static_cast<hipStream_t>(stream);
+    if (variant == MELD_AUTO && radix_sorts(ctx, payload != nullptr, n) && !capturing(s)) {
+        // Without the memory for its scratch, the network, which needs less.
+        if (ensure_words(&ctx->merge_buf, &ctx->merge_words,
+                         meld::radix_scratch_words((uint32_t)n, payload != nullptr),
+                         "radix scratch") == MELD_OK) {
+            hipError_t e =
+                meld::launch_radix_sort(keys, payload, (uint32_t)n, ctx->merge_buf, s);
+            if (e != hipSuccess) return hip_fail(e, "radix sort launch");
+            return MELD_OK;
+        }
+    }
     SortPlan plan = fixed_plan(ctx, payload != nullptr, n, variant);
     if (variant == MELD_AUTO) {
         meld_status st = auto_sort_plan(ctx, keys, payload, n, s, &plan);
@@ -1372,14 +1397,17 @@ meld_status meld_sort_plan_describe(meld_ctx *ctx, size_t n, int with_payload,
     const uint32_t log_n = n <= 1 ? 0 : log2_ceil(n);
     const bool m = variant == MELD_AUTO || use_melded(variant);
     SortPlan plan{default_log_tile(pairs, log_n), m, m, true};
-    bool tuned = false;
+    bool tuned = false, radix = false;
     if (ctx != nullptr) {
+        radix = variant == MELD_AUTO && radix_sorts(ctx, pairs, n);
         plan.log_t = plan_log_tile(ctx, pairs, log_n);
         plan.xch = plan_xch(ctx);
         if (variant == MELD_AUTO) tuned = cached_sort_plan(ctx, pairs, log_n, &plan);
     }
-    std::string d = fmt("{\"n\": %zu, \"log_n\": %u, \"pairs\": %s, \"tuned\": %s", n, log_n,
-                        pairs ? "true" : "false", tuned ? "true" : "false");
+    std::string d = fmt("{\"n\": %zu, \"log_n\": %u, \"pairs\": %s, \"tuned\": %s, "
+                        "\"sorts_by\": \"%s\"",
+                        n, log_n, pairs ? "true" : "false", tuned ? "true" : "false",
+                        radix ? "radix" : "network");
     uint32_t hbm = 0, steps = 0;
     std::string list;
     if (n > 1) {
