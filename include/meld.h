@@ -31,16 +31,15 @@
  *     asynchronous on it; results are ready once the stream has reached the
  *     call. Kernel faults surface at the caller's next synchronisation.
  *     Exception: a call that needs more context scratch than the context
- *     holds (the first non-power-of-two sort at a larger padding, a larger
- *     MELD_AUTO sort than before, a segmented sort over more segments than
- *     before, the first MELD_AUTO trials of a shape) waits for the device (hipDeviceSynchronize) before it
- *     frees the smaller buffer and allocates the larger one; later calls of
- *     that size or less are asynchronous. meld_sort_u32_noalloc never
- *     allocates or waits.
+ *     holds (a larger MELD_AUTO sort than before, a segmented sort over more
+ *     segments than before, the first MELD_AUTO trials of a shape) waits for
+ *     the device (hipDeviceSynchronize) before it frees the smaller buffer and
+ *     allocates the larger one; later calls of that size or less are
+ *     asynchronous. meld_sort_u32_noalloc never allocates or waits.
  *   - Argument errors are detected before anything is enqueued and return
  *     MELD_EINVAL with a message in meld_last_error(); the arrays are then
  *     untouched. A failed launch returns MELD_EHIP.
- *   - A context's scratch (sort tail, segmented-sort queues, merge and tuning
+ *   - A context's scratch (segmented-sort queues, radix, merge and tuning
  *     buffers) is shared by every call on it. Calls on one context must not
  *     overlap from several host threads, and must all be enqueued on one
  *     stream (or on streams ordered by events): two calls on one context on
@@ -126,9 +125,12 @@ const char *meld_last_error(void);
  * paper's running example (Motivating Example section, Figure 1): phases
  * k = 2, 4, ..., N and steps j = k/2, ..., 1 over N = the next power of two
  * >= n; element i is kept in ascending order when (i & k) == 0 and in
- * descending order otherwise, with strict compares. Positions n..N-1 hold
- * the value 0xFFFFFFFF (for pairs (0xFFFFFFFF, 0xFFFFFFFF)) in library
- * scratch; nothing past n is read or written in the caller's arrays.
+ * descending order otherwise, with strict compares. For an n that is no power
+ * of two the direction bit is (i ^ (n - 1)) & k instead, which keeps the
+ * block that holds the array's end ascending in every phase above the tile:
+ * the padding (0xFFFFFFFF, for pairs (0xFFFFFFFF, 0xFFFFFFFF)) never leaves
+ * the positions n..N-1, takes no memory and no work, and nothing past n is
+ * read or written in the caller's arrays.
  * MELD_AUTO runs the network up to 2^15 keys or 2^17 pairs, with
  * MELD_OPT_SORT_LOG_TILE or MELD_OPT_LANE_EXCHANGE set, under capture, and
  * where the scratch below cannot be allocated; otherwise a least-significant-
@@ -142,27 +144,21 @@ const char *meld_last_error(void);
  *          unique; with payload = original index this is a stable sort.
  * n:       number of elements, n < 2^31; n <= 1 is a no-op.
  * Errors:  MELD_EINVAL for NULL/host pointers when n > 1 or n >= 2^31;
- *          MELD_ENOMEM when scratch for a non-power-of-two n cannot be
- *          allocated.
+ *          MELD_ENOMEM when the scratch of MELD_AUTO's timed trials cannot
+ *          be allocated.
  */
 meld_status meld_sort_u32(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size_t n,
                           meld_variant variant, void *stream);
 
-/* Words of the device scratch behind meld_sort_u32_noalloc: 2^22 (16 MiB). */
+/* Most words of padding meld_sort_u32_noalloc accepts: 2^22. */
 #define MELD_NOALLOC_SCRATCH_WORDS (1u << 22)
 
 /* meld_sort_u32 for callers that cannot allocate device memory: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
- * It allocates nothing (no hipMalloc, hipFree or allocating library call):
- * the padding of a non-power-of-two n lives in a device array of the library
- * (MELD_NOALLOC_SCRATCH_WORDS u32, one copy per device, held until the
- * process ends, its address looked up by meld_create), filled with the
- * sentinel by a kernel on every call. The same network, forms and result as
- * meld_sort_u32; MELD_AUTO takes the tuner's decision for the shape if it
- * holds one and the melded default otherwise (it never times trials).
- * The array is shared by every call on the device, whatever the context:
- * calls that overlap on one GPU (other host threads, or streams that run
- * concurrently) race on it and must be ordered by the caller.
+ * It allocates nothing (no hipMalloc, hipFree or allocating library call)
+ * and uses no scratch. The same network, forms and result as meld_sort_u32;
+ * MELD_AUTO takes the tuner's decision for the shape if it holds one and the
+ * melded default otherwise (it never times trials).
  * Arguments and errors: as meld_sort_u32, plus MELD_EINVAL when the padding
  * (N - n words for keys, 2 (N - n) for pairs, N the next power of two >= n)
  * exceeds MELD_NOALLOC_SCRATCH_WORDS and n is above one tile (every n up to
@@ -173,8 +169,7 @@ meld_status meld_sort_u32_noalloc(meld_ctx *ctx, uint32_t *keys, uint32_t *paylo
 /* meld_sort_u32 with the duration of every launch: a HIP event is recorded
  * on `stream` before the first launch and after each one, the call waits for
  * the last, and launch_ms[i] receives the time between events i and i+1 in
- * milliseconds (launch i of the plan meld_sort_plan_describe lists; for a
- * non-power-of-two n the first also holds the fill of the padding). Used to
+ * milliseconds (launch i of the plan meld_sort_plan_describe lists). Used to
  * measure each kernel of the network against its roofline: it always runs the
  * network, for MELD_AUTO the tuned one. Synchronous.
  * launch_ms: host float[cap]; *n_launches receives the number of launches

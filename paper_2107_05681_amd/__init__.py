@@ -60,8 +60,8 @@ class SideRange(ctypes.Structure):
 
 _lib = None
 _lock = threading.Lock()
-# One library context per (device, stream): a context's scratch (sort tail,
-# segmented-sort queues, merge and tuning buffers) is shared by every call on
+# One library context per (device, stream): a context's scratch (segmented-sort
+# queues, radix, merge and tuning buffers) is shared by every call on
 # it, so calls on streams that may run concurrently must not share one.
 _ctxs: dict[tuple[int, int], ctypes.c_void_p] = {}
 _options: dict[int, dict[int, int]] = {}  # device -> option -> value, for every context

@@ -97,19 +97,12 @@ __global__ __launch_bounds__(NT) void bitonic_tile_kernel(SortArray a, uint32_t 
     const uint32_t T = 1u << log_t;
     const uint32_t base = blockIdx.x << log_t;
 
-    const bool below_n = MODE == kTail && base + T <= a.n;  // uniform per workgroup
-    if (below_n)
-        tile_load<PAIRS, kPlain, NT>(a, s, base, T);
-    else
-        tile_load<PAIRS, MODE, NT>(a, s, base, T);
+    tile_load<PAIRS, MODE, NT>(a, s, base, T);
     __syncthreads();
     lds_network<E, MELD_LO, MELD_HI, NT, true>(s, T, base, m_begin, m_end, j_first, step_limit,
                                               threadIdx.x);
     __syncthreads();
-    if (below_n)
-        tile_store<PAIRS, kPlain, NT>(a, s, base, T);
-    else
-        tile_store<PAIRS, MODE, NT>(a, s, base, T);
+    tile_store<PAIRS, MODE, NT>(a, s, base, T);
 }
 
 // Workgroup order of the streaming passes. Consecutive workgroups go to
@@ -140,11 +133,14 @@ __device__ __forceinline__ uint32_t xcd_run_index(uint32_t b, uint32_t count) {
 // Gathered streaming pass: C = L - S, so the steps act on array bits
 // b_lo .. b_lo + S - 1 and each of the 2^S rows is 2^C contiguous elements.
 // Both take their tiles in XCD runs (a gathered pass only where the middle
-// index has the bits for them).
+// index has the bits for them). Positions from `end` on (active_end) take no
+// part: the grid covers the blocks of 2^(b_lo + S) that start below it, and a
+// tile that starts at it or above has nothing to do.
 template <bool PAIRS, int L, int S, int C>
 __global__ __launch_bounds__(1 << (L - 4)) void bitonic_pass_regs_kernel(SortArray a, uint32_t m,
                                                                          uint32_t b_lo, int mode,
-                                                                         int32_t nsteps) {
+                                                                         int32_t nsteps,
+                                                                         uint32_t end) {
     using E = typename ElemOf<PAIRS>::type;
     extern __shared__ __align__(16) unsigned char smem[];
     E *s = reinterpret_cast<E *>(smem);
@@ -156,8 +152,9 @@ __global__ __launch_bounds__(1 << (L - 4)) void bitonic_pass_regs_kernel(SortArr
     else if (spread >= 3 + kXcdRunLogGather)
         b = xcd_run_index<kXcdRunLogGather>(b, gridDim.x);
     const uint32_t base = ((b & ((1u << spread) - 1)) << C) | ((b >> spread) << (b_lo + L - C));
+    if (base >= end) return;
     const TileMap<L, C> map{base, b_lo};
-    const bool up = ((base >> m) & 1u) == 0;
+    const bool up = (((base ^ a.dir) >> m) & 1u) == 0;
 
     E e[kMergeE];
     // The tile's loads go out at a raised wave priority: with two workgroups
@@ -178,14 +175,15 @@ __global__ __launch_bounds__(1 << (L - 4)) void bitonic_pass_regs_kernel(SortArr
 }
 
 template <bool PAIRS, int L>
-hipError_t launch_merge_l(const SortArray &a, uint32_t n_tiles, uint32_t m, int32_t nsteps,
-                          int io_mode, hipStream_t stream) {
+hipError_t launch_merge_l(const SortArray &a, uint32_t m, int32_t nsteps, int io_mode,
+                          hipStream_t stream) {
     const size_t lds = regs_lds_bytes<PAIRS, L>();
     auto kern = bitonic_pass_regs_kernel<PAIRS, L, L, L>;
     hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(n_tiles), dim3(1u << (L - 4)), lds, stream, a, m, (uint32_t)L,
-                       io_mode, nsteps);
+    const uint32_t end = active_end(a.n, m);
+    hipLaunchKernelGGL(kern, dim3(blocks_for(end, 1u << L)), dim3(1u << (L - 4)), lds, stream, a,
+                       m, (uint32_t)L, io_mode, nsteps, end);
     return hipGetLastError();
 }
 
@@ -206,16 +204,17 @@ hipError_t launch_gather_r(const SortArray &a, uint32_t log_n, uint32_t m, uint3
     auto kern = bitonic_pass_regs_kernel<PAIRS, L, R, C>;
     hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(1u << (log_n - L)), dim3(1u << (L - 4)), lds, stream, a, m,
-                       b_lo, io_mode, nsteps);
+    const uint32_t end = active_end(a.n, m);
+    hipLaunchKernelGGL(kern, dim3(blocks_for(end, 1u << (b_lo + R)) << (b_lo - C)),
+                       dim3(1u << (L - 4)), lds, stream, a, m, b_lo, io_mode, nsteps, end);
     return hipGetLastError();
 }
 
 template <bool PAIRS>
-hipError_t launch_merge_p(const SortArray &a, uint32_t log_t, uint32_t n_tiles, uint32_t m,
-                          int32_t nsteps, int io_mode, hipStream_t stream) {
+hipError_t launch_merge_p(const SortArray &a, uint32_t log_t, uint32_t m, int32_t nsteps,
+                          int io_mode, hipStream_t stream) {
 #define MELD_CASE(L) \
-    case L: return launch_merge_l<PAIRS, L>(a, n_tiles, m, nsteps, io_mode, stream);
+    case L: return launch_merge_l<PAIRS, L>(a, m, nsteps, io_mode, stream);
     switch (log_t) {
         MELD_REGS_SIZES(MELD_CASE)
         default: return hipErrorInvalidValue;
@@ -267,9 +266,12 @@ __global__ __launch_bounds__(kGlobalThreads) void bitonic_global_kernel(SortArra
     if (t >= n_threads) return;
     const uint32_t low = t & ((1u << b_lo) - 1);
     const uint32_t base = ((t >> b_lo) << (b_lo + R)) | low;
-    const bool up = ((base >> m) & 1u) == 0;
+    const bool up = (((base ^ a.dir) >> m) & 1u) == 0;
     E e[1 << R];
-    if constexpr (MODE == kPlain) {
+    // Lanes of a wave differ in low bits only, so all but the wave at position
+    // n agree on how many of their rows lie below n.
+    const bool below = MODE == kPlain || base + (((1u << R) - 1) << b_lo) < a.n;
+    if (below) {
         // Row q of every lane starts at the uniform address keys + (q << b_lo)
         // (a scalar base) and the lane adds its own 32-bit offset: one offset
         // register serves all 2^R rows, where per-element 64-bit addresses
@@ -285,7 +287,7 @@ __global__ __launch_bounds__(kGlobalThreads) void bitonic_global_kernel(SortArra
     } else {
 #pragma unroll
         for (int q = 0; q < (1 << R); ++q)
-            e[q] = load_elem<PAIRS, MODE, NT>(a, base + ((uint32_t)q << b_lo));
+            e[q] = load_elem<PAIRS, kPad, NT>(a, base + ((uint32_t)q << b_lo));
     }
 #pragma unroll
     for (int s = R - 1; s >= 0; --s) {
@@ -295,7 +297,7 @@ __global__ __launch_bounds__(kGlobalThreads) void bitonic_global_kernel(SortArra
                 if ((q & (1 << s)) == 0) cex_regs(e[q], e[q | (1 << s)], up);
         }
     }
-    if constexpr (MODE == kPlain) {
+    if (below) {
 #pragma unroll
         for (int q = 0; q < (1 << R); ++q) {
             if constexpr (PAIRS) {
@@ -308,7 +310,7 @@ __global__ __launch_bounds__(kGlobalThreads) void bitonic_global_kernel(SortArra
     } else {
 #pragma unroll
         for (int q = 0; q < (1 << R); ++q)
-            store_elem<PAIRS, MODE, NT>(a, base + ((uint32_t)q << b_lo), e[q]);
+            store_elem<PAIRS, kPad, NT>(a, base + ((uint32_t)q << b_lo), e[q]);
     }
 }
 
@@ -345,8 +347,7 @@ hipError_t launch_tile_t(const SortArray &a, uint32_t log_t, uint32_t n_tiles, u
     switch (io_mode) {
         MELD_TILE_MODE(kPlain)
         MELD_TILE_MODE(kPlainVec)
-        MELD_TILE_MODE(kTail)
-        MELD_TILE_MODE(kSentinel)
+        MELD_TILE_MODE(kPad)
         default:
             return hipErrorInvalidValue;
     }
@@ -389,9 +390,9 @@ hipError_t launch_tile_p(const SortArray &a, uint32_t log_t, uint32_t n_tiles, u
 }
 
 template <bool PAIRS, int R, int MODE>
-hipError_t launch_global_r(const SortArray &a, uint32_t log_n, uint32_t m, uint32_t b_lo,
-                           int32_t step_limit, hipStream_t stream) {
-    const uint32_t n_threads = 1u << (log_n - R);
+hipError_t launch_global_r(const SortArray &a, uint32_t m, uint32_t b_lo, int32_t step_limit,
+                           hipStream_t stream) {
+    const uint32_t n_threads = blocks_for(active_end(a.n, m), 1u << (b_lo + R)) << b_lo;
     const uint32_t blocks = (n_threads + kGlobalThreads - 1) / kGlobalThreads;
     const int32_t nsteps = step_limit < 0 ? R : step_limit;
     if (a.nt != 0)
@@ -404,15 +405,15 @@ hipError_t launch_global_r(const SortArray &a, uint32_t log_n, uint32_t m, uint3
 }
 
 template <bool PAIRS, int MODE>
-hipError_t launch_global_p(const SortArray &a, uint32_t log_n, uint32_t m, uint32_t b_hi,
-                           uint32_t b_lo, int32_t step_limit, hipStream_t stream) {
+hipError_t launch_global_p(const SortArray &a, uint32_t m, uint32_t b_hi, uint32_t b_lo,
+                           int32_t step_limit, hipStream_t stream) {
     switch (b_hi - b_lo + 1) {
-        case 1: return launch_global_r<PAIRS, 1, MODE>(a, log_n, m, b_lo, step_limit, stream);
-        case 2: return launch_global_r<PAIRS, 2, MODE>(a, log_n, m, b_lo, step_limit, stream);
-        case 3: return launch_global_r<PAIRS, 3, MODE>(a, log_n, m, b_lo, step_limit, stream);
-        case 4: return launch_global_r<PAIRS, 4, MODE>(a, log_n, m, b_lo, step_limit, stream);
-        case 5: return launch_global_r<PAIRS, 5, MODE>(a, log_n, m, b_lo, step_limit, stream);
-        case 6: return launch_global_r<PAIRS, 6, MODE>(a, log_n, m, b_lo, step_limit, stream);
+        case 1: return launch_global_r<PAIRS, 1, MODE>(a, m, b_lo, step_limit, stream);
+        case 2: return launch_global_r<PAIRS, 2, MODE>(a, m, b_lo, step_limit, stream);
+        case 3: return launch_global_r<PAIRS, 3, MODE>(a, m, b_lo, step_limit, stream);
+        case 4: return launch_global_r<PAIRS, 4, MODE>(a, m, b_lo, step_limit, stream);
+        case 5: return launch_global_r<PAIRS, 5, MODE>(a, m, b_lo, step_limit, stream);
+        case 6: return launch_global_r<PAIRS, 6, MODE>(a, m, b_lo, step_limit, stream);
         default: return hipErrorInvalidValue;
     }
 }
@@ -425,6 +426,7 @@ hipError_t launch_bitonic_tile(const SortArray &a, uint32_t log_t, uint32_t n_ti
                                int threads, hipStream_t stream) {
     if (n_tiles == 0 || step_limit == 0) return hipSuccess;
     if (io_mode == kPlainVec && log_t < 2) io_mode = kPlain;
+    if (io_mode == kPadVec) io_mode = kPad;
     if (a.vals != nullptr)
         return launch_tile_p<true>(a, log_t, n_tiles, m_begin, m_end, j_first, step_limit, meld_lo,
                                    meld_hi, io_mode, threads, stream);
@@ -432,15 +434,15 @@ hipError_t launch_bitonic_tile(const SortArray &a, uint32_t log_t, uint32_t n_ti
                                 meld_hi, io_mode, threads, stream);
 }
 
-hipError_t launch_bitonic_global(const SortArray &a, uint32_t log_n, uint32_t m, uint32_t b_hi,
-                                 uint32_t b_lo, int32_t step_limit, hipStream_t stream) {
+hipError_t launch_bitonic_global(const SortArray &a, uint32_t m, uint32_t b_hi, uint32_t b_lo,
+                                 int32_t step_limit, int io_mode, hipStream_t stream) {
     if (step_limit == 0) return hipSuccess;
-    const bool tail = a.tk != nullptr;
+    const bool pad = io_mode == kPad || io_mode == kPadVec;
     if (a.vals != nullptr)
-        return tail ? launch_global_p<true, kTail>(a, log_n, m, b_hi, b_lo, step_limit, stream)
-                    : launch_global_p<true, kPlain>(a, log_n, m, b_hi, b_lo, step_limit, stream);
-    return tail ? launch_global_p<false, kTail>(a, log_n, m, b_hi, b_lo, step_limit, stream)
-                : launch_global_p<false, kPlain>(a, log_n, m, b_hi, b_lo, step_limit, stream);
+        return pad ? launch_global_p<true, kPad>(a, m, b_hi, b_lo, step_limit, stream)
+                   : launch_global_p<true, kPlain>(a, m, b_hi, b_lo, step_limit, stream);
+    return pad ? launch_global_p<false, kPad>(a, m, b_hi, b_lo, step_limit, stream)
+               : launch_global_p<false, kPlain>(a, m, b_hi, b_lo, step_limit, stream);
 }
 
 hipError_t launch_bitonic_sort_regs(const SortArray &a, uint32_t log_t, uint32_t n_tiles,
@@ -456,8 +458,6 @@ hipError_t launch_bitonic_gather(const SortArray &a, uint32_t log_n, uint32_t m,
                                  uint32_t b_lo, int32_t step_limit, int io_mode,
                                  hipStream_t stream) {
     if (step_limit == 0) return hipSuccess;
-    if (io_mode == kPlain) io_mode = kTail;
-    if (io_mode != kTail && io_mode != kPlainVec) return hipErrorInvalidValue;
     const int32_t r = (int32_t)(b_hi - b_lo + 1);
     const int32_t nsteps = step_limit < 0 ? r : step_limit;
     if (a.vals != nullptr) {
@@ -477,13 +477,12 @@ hipError_t launch_bitonic_gather(const SortArray &a, uint32_t log_n, uint32_t m,
     }
 }
 
-hipError_t launch_bitonic_merge(const SortArray &a, uint32_t log_t, uint32_t n_tiles, uint32_t m,
+hipError_t launch_bitonic_merge(const SortArray &a, uint32_t log_t, uint32_t m,
                                 int32_t step_limit, int io_mode, hipStream_t stream) {
-    if (n_tiles == 0 || step_limit == 0) return hipSuccess;
-    if (io_mode == kPlain) io_mode = kTail;
+    if (a.n == 0 || step_limit == 0) return hipSuccess;
     const int32_t nsteps = step_limit < 0 ? (int32_t)log_t : step_limit;
-    if (a.vals != nullptr) return launch_merge_p<true>(a, log_t, n_tiles, m, nsteps, io_mode, stream);
-    return launch_merge_p<false>(a, log_t, n_tiles, m, nsteps, io_mode, stream);
+    if (a.vals != nullptr) return launch_merge_p<true>(a, log_t, m, nsteps, io_mode, stream);
+    return launch_merge_p<false>(a, log_t, m, nsteps, io_mode, stream);
 }
 
 hipError_t launch_fill_u32(uint32_t *p, uint32_t value, size_t count, hipStream_t stream) {

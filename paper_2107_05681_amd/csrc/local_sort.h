@@ -141,7 +141,7 @@ __device__ __forceinline__ void lds_phases(E (&e)[kMergeE], E *s, uint32_t t, ui
 }
 
 // The whole network of a tile of T = 2^L elements (phases k = 2 .. T; the
-// last one's direction is bit L of the tile's base).
+// last one's direction is bit L of the tile's base and the array's dir).
 //
 // XCH = false: phases k <= 64 run as the LDS comparator network, one
 // comparator per lane per iteration (Figure 1's mapping), in form MELD_LO:
@@ -170,9 +170,10 @@ __global__ __launch_bounds__(1 << (L - 4)) void bitonic_sort_regs_kernel(SortArr
     extern __shared__ __align__(16) unsigned char smem[];
     E *s = reinterpret_cast<E *>(smem);
     const uint32_t t = threadIdx.x;
-    const uint32_t base = blockIdx.x * T;
+    // Only the last phase looks above the tile: there the array's direction holds.
+    const uint32_t base = (blockIdx.x * T) ^ (a.dir & ~(T - 1));
 
-    const TileMap<L, L> map{base, (uint32_t)L};
+    const TileMap<L, L> map{blockIdx.x * T, (uint32_t)L};
     E e[kMergeE];
     regs_load<PAIRS, L, L>(a, map, t, mode, e);
     if constexpr (XCH) {
@@ -247,7 +248,6 @@ hipError_t launch_sort_regs_path(const SortArray &a, uint32_t log_t, uint32_t n_
                                  int32_t step_limit, bool meld_lo, bool meld_hi, int io_mode,
                                  hipStream_t stream) {
     if (n_tiles == 0 || step_limit == 0) return hipSuccess;
-    if (io_mode == kPlain) io_mode = kTail;  // no tail workspace: every tile is below n
     if (a.vals != nullptr)
         return launch_sort_regs_p<true, XCH>(a, log_t, n_tiles, step_limit, meld_lo, meld_hi,
                                              io_mode, stream);

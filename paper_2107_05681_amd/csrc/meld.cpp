@@ -20,9 +20,6 @@ using meld::SortArray;
 
 struct meld_ctx {
     int device = 0;
-    // Tail workspace backing the virtual padding of non-power-of-two sorts.
-    uint32_t *tail = nullptr;
-    size_t tail_words = 0;
     // Segmented sort: queue state, per-segment class and queue, and the
     // per-workgroup padding scratch of the persistent grid.
     meld::SegState *seg_state = nullptr;
@@ -73,37 +70,6 @@ constexpr size_t kNontemporalBytes = (size_t)256 << 20;
 // Tie window of the sort tuner's second round (relative): the spread of the
 // medians of five or nine timed local-sort launches on one MI355X.
 constexpr double kFinalTie = 0.005;
-
-// Scratch of meld_sort_u32_noalloc: the padding of a non-power-of-two sort,
-// in a device array of the library itself, so that the call allocates
-// nothing. Every device holds its own copy until the process ends; host code
-// reaches a device's copy only through the address hipGetSymbolAddress gives
-// for it (the array's name is not a device address in host code).
-constexpr size_t kNoAllocWords = MELD_NOALLOC_SCRATCH_WORDS;
-__device__ __align__(256) uint32_t scratch[kNoAllocWords];
-
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mu;
-uint32_t *g_scratch_ptr[kMaxDevices] = {};
-
-// Looks up device `device`'s copy of the scratch array once; the device must
-// be current.
-hipError_t noalloc_scratch_init(int device) {
-    if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (g_scratch_ptr[device] != nullptr) return hipSuccess;
-    void *ptr = nullptr;
-    hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
-    if (e != hipSuccess) return e;
-    g_scratch_ptr[device] = static_cast<uint32_t *>(ptr);
-    return hipSuccess;
-}
-
-uint32_t *noalloc_scratch(int device) {
-    if (device < 0 || device >= kMaxDevices) return nullptr;
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    return g_scratch_ptr[device];
-}
 
 }  // namespace
 
@@ -156,25 +122,6 @@ struct DeviceGuard {
         if (prev >= 0) (void)hipSetDevice(prev);
     }
 };
-
-meld_status ensure_tail(meld_ctx *ctx, size_t words) {
-    if (words <= ctx->tail_words) return MELD_OK;
-    if (ctx->tail != nullptr) {
-        hipError_t e = hipDeviceSynchronize();
-        if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
-        (void)hipFree(ctx->tail);
-        ctx->tail = nullptr;
-        ctx->tail_words = 0;
-    }
-    void *p = nullptr;
-    if (hipMalloc(&p, words * sizeof(uint32_t)) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(MELD_ENOMEM, "cannot allocate %zu bytes of sort scratch", words * 4);
-    }
-    ctx->tail = static_cast<uint32_t *>(p);
-    ctx->tail_words = words;
-    return MELD_OK;
-}
 
 bool use_melded(meld_variant v) { return v != MELD_DIVERGENT; }
 
@@ -585,14 +532,10 @@ std::vector<SortPass> sort_passes(const SortPlan &plan, bool pairs, uint32_t log
 
 // Enqueues the whole network (or its first step_limit steps) on keys[0..n).
 // marks: NULL, or one event per launch plus one, recorded on the stream
-// before the first launch (and the tail fill) and after every launch.
-// fixed_tail: NULL (the context's tail workspace, grown on demand), or device
-// memory of fixed_tail_words words that holds the padding instead (nothing is
-// allocated; MELD_EINVAL if it is too small).
+// before the first launch and after every launch. Allocates nothing.
 meld_status sort_impl(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size_t n,
                       const SortPlan &plan, int64_t step_limit, hipStream_t stream,
-                      const std::vector<hipEvent_t> *marks = nullptr,
-                      uint32_t *fixed_tail = nullptr, size_t fixed_tail_words = 0) {
+                      const std::vector<hipEvent_t> *marks = nullptr) {
     const bool pairs = payload != nullptr;
     const uint32_t log_n = log2_ceil(n);
     const size_t big_n = (size_t)1 << log_n;
@@ -600,7 +543,11 @@ meld_status sort_impl(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size_t n
     // Nontemporal accesses once the array outgrows the caches (L2 and the
     // 256 MB Infinity Cache); below, the array stays cached between launches.
     const bool nt = big_n * (pairs ? 8 : 4) > kNontemporalBytes;
-    SortArray a{keys, payload, nullptr, nullptr, (uint32_t)n, nt ? 1u : 0u};
+    const bool padded = big_n > n;
+    SortArray a{keys, payload, (uint32_t)n, padded ? (uint32_t)n - 1 : 0u, nt ? 1u : 0u};
+    const bool vec = aligned16(keys) && (!pairs || aligned16(payload));
+    const int io = padded ? (vec ? meld::kIoPadVec : meld::kIoPad)
+                          : (vec ? meld::kIoPlainVec : meld::kIoPlain);
     int64_t left = step_limit;  // < 0: unlimited
     auto take = [&left](uint64_t steps) -> int32_t {
         if (left < 0) return -1;
@@ -622,11 +569,8 @@ meld_status sort_impl(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size_t n
 
     hipError_t e;
     if (passes[0].kind == PassKind::kTile) {
-        // One tile holds everything; positions >= n are sentinels.
+        // One tile holds everything.
         const uint32_t log_t = std::max<uint32_t>(log_n, 1);
-        const int io = big_n > n ? meld::kIoSentinel
-                       : (aligned16(keys) && (!pairs || aligned16(payload))) ? meld::kIoPlainVec
-                                                                             : meld::kIoPlain;
         const int32_t steps = take(passes[0].steps);
         e = mark(0);
         if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
@@ -641,33 +585,11 @@ meld_status sort_impl(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size_t n
         return MELD_OK;
     }
 
-    if (big_n > n) {
-        const size_t pad = big_n - n;
-        const size_t words = pairs ? 2 * pad : pad;
-        uint32_t *tail = fixed_tail;
-        if (tail == nullptr) {
-            meld_status st = ensure_tail(ctx, words);
-            if (st != MELD_OK) return st;
-            tail = ctx->tail;
-        } else if (words > fixed_tail_words) {
-            return fail(MELD_EINVAL, "sort: padding of %zu words exceeds the %zu-word scratch",
-                        words, fixed_tail_words);
-        }
-        a.tk = tail;
-        a.tv = pairs ? tail + pad : nullptr;
-        e = mark(0);
-        if (e == hipSuccess) e = meld::launch_fill_u32(tail, 0xFFFFFFFFu, words, stream);
-        if (e != hipSuccess) return hip_fail(e, "fill launch");
-    } else {
-        e = mark(0);
-        if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
-    }
+    e = mark(0);
+    if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
 
     const uint32_t log_t = plan.log_t;
-    const uint32_t n_tiles = (uint32_t)(big_n >> log_t);
-    const int io = a.tk != nullptr ? meld::kIoTail
-                   : (aligned16(keys) && (!pairs || aligned16(payload))) ? meld::kIoPlainVec
-                                                                         : meld::kIoPlain;
+    const uint32_t n_tiles = (uint32_t)((n + ((size_t)1 << log_t) - 1) >> log_t);
     for (size_t pi = 0; pi < passes.size(); ++pi) {
         const SortPass &p = passes[pi];
         const int32_t steps = take(p.steps);
@@ -680,10 +602,10 @@ meld_status sort_impl(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size_t n
                 e = meld::launch_bitonic_gather(a, log_n, p.m, p.b_hi, p.b_lo, steps, io, stream);
                 break;
             case PassKind::kRegs:
-                e = meld::launch_bitonic_global(a, log_n, p.m, p.b_hi, p.b_lo, steps, stream);
+                e = meld::launch_bitonic_global(a, p.m, p.b_hi, p.b_lo, steps, io, stream);
                 break;
             case PassKind::kMerge:
-                e = meld::launch_bitonic_merge(a, log_t, n_tiles, p.m, steps, io, stream);
+                e = meld::launch_bitonic_merge(a, log_t, p.m, steps, io, stream);
                 break;
             default:
                 return fail(MELD_EINVAL, "sort: unexpected pass");
@@ -1235,11 +1157,6 @@ meld_status meld_create(int hip_device, meld_ctx **out) {
     if (hip_device < 0 || hip_device >= count)
         return fail(MELD_EINVAL, "meld_create: device %d out of range (%d devices)", hip_device,
                     count);
-    {
-        DeviceGuard g(hip_device);
-        e = noalloc_scratch_init(hip_device);
-        if (e != hipSuccess) return hip_fail(e, "meld_create: address of the device scratch");
-    }
     meld_ctx *ctx = new (std::nothrow) meld_ctx();
     if (ctx == nullptr) return fail(MELD_ENOMEM, "meld_create: out of host memory");
     ctx->device = hip_device;
@@ -1266,7 +1183,7 @@ void meld_destroy(meld_ctx *ctx) {
     (void)hipDeviceSynchronize();
     drop_seg_graphs(ctx);
     if (ctx->capture_stream != nullptr) (void)hipStreamDestroy(ctx->capture_stream);
-    for (void *p : {(void *)ctx->tail, (void *)ctx->seg_state, (void *)ctx->seg_cls,
+    for (void *p : {(void *)ctx->seg_state, (void *)ctx->seg_cls,
                     (void *)ctx->seg_queue, (void *)ctx->seg_work, (void *)ctx->tune_buf,
                     (void *)ctx->merge_buf, (void *)ctx->merge_cuts, (void *)ctx->probe_buf})
         if (p != nullptr) (void)hipFree(p);
@@ -1325,16 +1242,14 @@ meld_status meld_sort_u32_noalloc(meld_ctx *ctx, uint32_t *keys, uint32_t *paylo
     if (variant == MELD_AUTO) (void)cached_sort_plan(ctx, pairs, log_n, &plan);
     const size_t pad = ((size_t)1 << log_n) - n;
     const size_t words = pairs ? 2 * pad : pad;
-    const bool one_tile = log_n <= plan.log_t;  // padded in LDS, no scratch
-    if (!one_tile && words > kNoAllocWords)
+    // The documented limit of the call, although the padding takes no memory.
+    const bool one_tile = log_n <= plan.log_t;
+    if (!one_tile && words > MELD_NOALLOC_SCRATCH_WORDS)
         return fail(MELD_EINVAL,
                     "%s: n = %zu needs %zu words of padding, above the %zu-word scratch "
                     "(MELD_NOALLOC_SCRATCH_WORDS); use meld_sort_u32",
-                    name, n, words, kNoAllocWords);
-    uint32_t *tail = noalloc_scratch(ctx->device);
-    if (tail == nullptr) return fail(MELD_EHIP, "%s: no device scratch on device %d", name, ctx->device);
-    return sort_impl(ctx, keys, payload, n, plan, -1, static_cast<hipStream_t>(stream), nullptr,
-                     tail, kNoAllocWords);
+                    name, n, words, (size_t)MELD_NOALLOC_SCRATCH_WORDS);
+    return sort_impl(ctx, keys, payload, n, plan, -1, static_cast<hipStream_t>(stream));
 }
 
 meld_status meld_sort_u32_timed(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size_t n,

@@ -30,11 +30,11 @@ struct ElemOf<true> {
 //   kPlain     every position is below n: direct loads and stores.
 //   kPlainVec  as kPlain, with 16-byte aligned arrays: tiles move 4 elements
 //              per lane per access.
-//   kTail      positions >= n live in the tail workspace: the address is
-//              selected per element (no branch).
-//   kSentinel  positions >= n read as the sentinel and are never stored
-//              (a single tile padded in LDS).
-enum IoMode { kPlain = kIoPlain, kPlainVec = kIoPlainVec, kTail = kIoTail, kSentinel = kIoSentinel };
+//   kPad       positions >= n read as the sentinel and are never stored; a
+//              tile wholly below n moves as in the plain modes.
+//   kPadVec    as kPad, with 16-byte aligned arrays: groups of 4 elements
+//              wholly below n move in one access.
+enum IoMode { kPlain = kIoPlain, kPlainVec = kIoPlainVec, kPad = kIoPad, kPadVec = kIoPadVec };
 
 // Global accesses of the streaming passes, the merge tails and the tile
 // sorts of a large array (SortArray::nt, set when the array is far larger
@@ -78,36 +78,23 @@ __device__ __forceinline__ void st16(uint32_t *p, uint4 v) {
 }
 
 template <int MODE, bool NT = false>
-__device__ __forceinline__ uint32_t ld_u32(const uint32_t *main, const uint32_t *tail, uint32_t n,
-                                           uint32_t p) {
-    if constexpr (MODE == kTail) {
-        const uint32_t *src = p < n ? main + p : tail + (p - n);
-        return ld4<NT>(src);
-    } else if constexpr (MODE == kSentinel) {
-        return p < n ? main[p] : kPadValue;
-    } else {
+__device__ __forceinline__ uint32_t ld_u32(const uint32_t *main, uint32_t n, uint32_t p) {
+    if constexpr (MODE == kPad)
+        return p < n ? ld4<NT>(main + p) : kPadValue;
+    else
         return ld4<NT>(main + p);
-    }
 }
 
 template <int MODE, bool NT = false>
-__device__ __forceinline__ void st_u32(uint32_t *main, uint32_t *tail, uint32_t n, uint32_t p,
-                                       uint32_t v) {
-    if constexpr (MODE == kTail) {
-        uint32_t *dst = p < n ? main + p : tail + (p - n);
-        st4<NT>(dst, v);
-    } else if constexpr (MODE == kSentinel) {
-        if (p < n) main[p] = v;
-    } else {
-        st4<NT>(main + p, v);
-    }
+__device__ __forceinline__ void st_u32(uint32_t *main, uint32_t n, uint32_t p, uint32_t v) {
+    if (MODE != kPad || p < n) st4<NT>(main + p, v);
 }
 
 template <bool PAIRS, int MODE, bool NT = false>
 __device__ __forceinline__ typename ElemOf<PAIRS>::type load_elem(const SortArray &a, uint32_t p) {
-    const uint32_t k = ld_u32<MODE, NT>(a.keys, a.tk, a.n, p);
+    const uint32_t k = ld_u32<MODE, NT>(a.keys, a.n, p);
     if constexpr (PAIRS) {
-        const uint32_t v = ld_u32<MODE, NT>(a.vals, a.tv, a.n, p);
+        const uint32_t v = ld_u32<MODE, NT>(a.vals, a.n, p);
         return ((uint64_t)k << 32) | v;
     } else {
         return k;
@@ -118,10 +105,35 @@ template <bool PAIRS, int MODE, bool NT = false>
 __device__ __forceinline__ void store_elem(const SortArray &a, uint32_t p,
                                            typename ElemOf<PAIRS>::type e) {
     if constexpr (PAIRS) {
-        st_u32<MODE, NT>(a.keys, a.tk, a.n, p, (uint32_t)(e >> 32));
-        st_u32<MODE, NT>(a.vals, a.tv, a.n, p, (uint32_t)e);
+        st_u32<MODE, NT>(a.keys, a.n, p, (uint32_t)(e >> 32));
+        st_u32<MODE, NT>(a.vals, a.n, p, (uint32_t)e);
     } else {
-        st_u32<MODE, NT>(a.keys, a.tk, a.n, p, e);
+        st_u32<MODE, NT>(a.keys, a.n, p, e);
+    }
+}
+
+// The 16-byte group at p (a multiple of 4), whose positions >= n are padding.
+template <bool NT>
+__device__ __forceinline__ uint4 ld16_pad(const uint32_t *main, uint32_t n, uint32_t p) {
+    uint4 v = make_uint4(kPadValue, kPadValue, kPadValue, kPadValue);
+    if (p + 4 <= n) {
+        v = ld16<NT>(main + p);
+    } else if (p < n) {
+        v.x = main[p];
+        if (p + 1 < n) v.y = main[p + 1];
+        if (p + 2 < n) v.z = main[p + 2];
+    }
+    return v;
+}
+
+template <bool NT>
+__device__ __forceinline__ void st16_pad(uint32_t *main, uint32_t n, uint32_t p, uint4 v) {
+    if (p + 4 <= n) {
+        st16<NT>(main + p, v);
+    } else if (p < n) {
+        main[p] = v.x;
+        if (p + 1 < n) main[p + 1] = v.y;
+        if (p + 2 < n) main[p + 2] = v.z;
     }
 }
 
@@ -307,22 +319,32 @@ __device__ __forceinline__ uint32_t window_tpart(uint32_t t, uint32_t B) {
     return (t & ((1u << B) - 1)) | ((t >> B) << (B + 4));
 }
 
+// Whether a mode moves a tile in 16-byte groups.
+__device__ __forceinline__ bool moves_vec(int mode) { return mode == kPlainVec || mode == kPadVec; }
+
+// Whether every position of a tile is below n (its map is increasing). A tile
+// in one of the plain modes always is.
+template <int L, int C>
+__device__ __forceinline__ bool tile_below(const SortArray &a, const TileMap<L, C> &map) {
+    return map((1u << L) - 1) < a.n;
+}
+
 // Thread t's 16 elements of a tile in layout V (C >= 2, so each 16-byte
-// group is contiguous in the array). Modes: vector (16-byte groups),
-// sentinel (positions >= n read as the pad value), plain or tail (positions
-// >= n from the tail workspace; a tile wholly below n loads directly).
+// group is contiguous in the array): in 16-byte groups or one by one, with the
+// checks against n only in the tile that holds position n.
 template <bool PAIRS, int L, int C, bool NT>
 __device__ __forceinline__ void regs_load_t(const SortArray &a, const TileMap<L, C> &map,
                                             uint32_t t, int mode,
                                             typename ElemOf<PAIRS>::type (&e)[kMergeE]) {
     using E = typename ElemOf<PAIRS>::type;
-    if (mode == kPlainVec) {
+    const bool below = tile_below(a, map);
+    auto groups = [&](auto load) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const uint32_t p = map(merge_index<L, -1>(t, 4 * c));
-            const uint4 k = ld16<NT>(a.keys + p);
+            const uint4 k = load(a.keys, p);
             if constexpr (PAIRS) {
-                const uint4 v = ld16<NT>(a.vals + p);
+                const uint4 v = load(a.vals, p);
                 e[4 * c + 0] = ((E)k.x << 32) | v.x;
                 e[4 * c + 1] = ((E)k.y << 32) | v.y;
                 e[4 * c + 2] = ((E)k.z << 32) | v.z;
@@ -334,17 +356,20 @@ __device__ __forceinline__ void regs_load_t(const SortArray &a, const TileMap<L,
                 e[4 * c + 3] = k.w;
             }
         }
-    } else if (mode == kSentinel) {
+    };
+    if (moves_vec(mode)) {
+        if (below)
+            groups([&](const uint32_t *p, uint32_t i) { return ld16<NT>(p + i); });
+        else
+            groups([&](const uint32_t *p, uint32_t i) { return ld16_pad<NT>(p, a.n, i); });
+    } else if (below) {
 #pragma unroll
         for (int r = 0; r < kMergeE; ++r)
-            e[r] = load_elem<PAIRS, kSentinel>(a, map(merge_index<L, -1>(t, r)));
+            e[r] = load_elem<PAIRS, kPlain, NT>(a, map(merge_index<L, -1>(t, r)));
     } else {
-        const bool below_n = map((1u << L) - 1) < a.n;  // the map is increasing
 #pragma unroll
-        for (int r = 0; r < kMergeE; ++r) {
-            const uint32_t p = map(merge_index<L, -1>(t, r));
-            e[r] = below_n ? load_elem<PAIRS, kPlain, NT>(a, p) : load_elem<PAIRS, kTail, NT>(a, p);
-        }
+        for (int r = 0; r < kMergeE; ++r)
+            e[r] = load_elem<PAIRS, kPad, NT>(a, map(merge_index<L, -1>(t, r)));
     }
 }
 
@@ -362,37 +387,36 @@ template <bool PAIRS, int L, int C, bool NT>
 __device__ __forceinline__ void regs_store_t(const SortArray &a, const TileMap<L, C> &map,
                                              uint32_t t, int mode,
                                              typename ElemOf<PAIRS>::type (&e)[kMergeE]) {
-    if (mode == kPlainVec) {
+    const bool below = tile_below(a, map);
+    auto groups = [&](auto store) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const uint32_t p = map(merge_index<L, -1>(t, 4 * c));
             if constexpr (PAIRS) {
-                st16<NT>(a.keys + p, make_uint4((uint32_t)(e[4 * c] >> 32),
-                                                (uint32_t)(e[4 * c + 1] >> 32),
-                                                (uint32_t)(e[4 * c + 2] >> 32),
-                                                (uint32_t)(e[4 * c + 3] >> 32)));
-                st16<NT>(a.vals + p, make_uint4((uint32_t)e[4 * c], (uint32_t)e[4 * c + 1],
-                                                (uint32_t)e[4 * c + 2], (uint32_t)e[4 * c + 3]));
+                store(a.keys, p,
+                      make_uint4((uint32_t)(e[4 * c] >> 32), (uint32_t)(e[4 * c + 1] >> 32),
+                                 (uint32_t)(e[4 * c + 2] >> 32), (uint32_t)(e[4 * c + 3] >> 32)));
+                store(a.vals, p,
+                      make_uint4((uint32_t)e[4 * c], (uint32_t)e[4 * c + 1],
+                                 (uint32_t)e[4 * c + 2], (uint32_t)e[4 * c + 3]));
             } else {
-                st16<NT>(a.keys + p, make_uint4(e[4 * c], e[4 * c + 1], e[4 * c + 2], e[4 * c + 3]));
+                store(a.keys, p, make_uint4(e[4 * c], e[4 * c + 1], e[4 * c + 2], e[4 * c + 3]));
             }
         }
-        return;
-    }
-    if (mode == kSentinel) {
+    };
+    if (moves_vec(mode)) {
+        if (below)
+            groups([&](uint32_t *p, uint32_t i, uint4 v) { st16<NT>(p + i, v); });
+        else
+            groups([&](uint32_t *p, uint32_t i, uint4 v) { st16_pad<NT>(p, a.n, i, v); });
+    } else if (below) {
 #pragma unroll
         for (int r = 0; r < kMergeE; ++r)
-            store_elem<PAIRS, kSentinel>(a, map(merge_index<L, L - 4>(t, r)), e[r]);
+            store_elem<PAIRS, kPlain, NT>(a, map(merge_index<L, L - 4>(t, r)), e[r]);
     } else {
-        const bool below_n = map((1u << L) - 1) < a.n;
 #pragma unroll
-        for (int r = 0; r < kMergeE; ++r) {
-            const uint32_t p = map(merge_index<L, L - 4>(t, r));
-            if (below_n)
-                store_elem<PAIRS, kPlain, NT>(a, p, e[r]);
-            else
-                store_elem<PAIRS, kTail, NT>(a, p, e[r]);
-        }
+        for (int r = 0; r < kMergeE; ++r)
+            store_elem<PAIRS, kPad, NT>(a, map(merge_index<L, L - 4>(t, r)), e[r]);
     }
 }
 
@@ -402,7 +426,7 @@ template <bool PAIRS, int L, int C, int FROM>
 __device__ __forceinline__ void regs_store(const SortArray &a, typename ElemOf<PAIRS>::type *s,
                                            const TileMap<L, C> &map, uint32_t t, int mode,
                                            typename ElemOf<PAIRS>::type (&e)[kMergeE]) {
-    if (mode == kPlainVec) {
+    if (moves_vec(mode)) {
         if constexpr (FROM != -1) merge_transpose<L, FROM, -1>(e, s, t);
     } else {
         merge_transpose<L, FROM, L - 4>(e, s, t);
