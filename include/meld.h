@@ -245,8 +245,9 @@ meld_status meld_segmented_sort_u32(meld_ctx *ctx, uint32_t *keys, size_t n_keys
  * three-way region (lower end of a comparator, upper end, idle): the
  * divergent form runs it as an if / else-if with one LDS load per side, the
  * melded form replicates the idle path into the two aligned sides and runs
- * one load from a selected address. MELD_AUTO times both forms once per shape
- * class on a scratch copy.
+ * one load from a selected address. MELD_AUTO with all steps sorts the buckets
+ * by a bitonic network in registers, which gives the same (unique) result; with
+ * max_steps it times both forms once per shape class on a scratch copy.
  *
  * keys:       device u32[n], n < 2^31; the last bucket may be ragged (its
  *             missing positions act as 0xFFFFFFFF and are never written).

@@ -131,6 +131,12 @@ size_t radix_scratch_words(uint32_t n, bool pairs);
 hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t n, uint32_t *scratch,
                              hipStream_t stream);
 
+// Every 2^log_bucket keys of keys[0..n) sorted ascending (log_bucket in 6..14;
+// the last bucket may be short), in registers (bucket_sort.hip). The array may
+// have any 4-byte alignment.
+hipError_t launch_bucket_sort(uint32_t *keys, uint32_t n, uint32_t log_bucket,
+                              hipStream_t stream);
+
 hipError_t launch_fill_u32(uint32_t *p, uint32_t value, size_t count, hipStream_t stream);
 
 // Seeded inputs generated on the device (gen.hip).

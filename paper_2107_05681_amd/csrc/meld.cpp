@@ -1366,6 +1366,14 @@ meld_status meld_oddeven_sort_buckets_u32(meld_ctx *ctx, uint32_t *keys, size_t 
         return fail(MELD_EINVAL, "%s: keys is not a device pointer on device %d", name,
                     ctx->device);
     const hipStream_t s = static_cast<hipStream_t>(stream);
+    // All steps: only the sorted buckets count. 2^26 keys, buckets of 2^6 / 2^11 /
+    // 2^14, without the copy of the input: 81 / 153 / 266 us in registers, 393 /
+    // 614 / 1455 us by the faster form of the network; no size where it is slower.
+    if (variant == MELD_AUTO && max_steps < 0) {
+        hipError_t e = meld::launch_bucket_sort(keys, (uint32_t)n, log_bucket, s);
+        if (e != hipSuccess) return hip_fail(e, "bucket sort launch");
+        return MELD_OK;
+    }
     bool melded = use_melded(variant);
     if (variant == MELD_AUTO) {
         auto run = [&](uint32_t *k, bool m) -> meld_status {

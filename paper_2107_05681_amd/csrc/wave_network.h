@@ -1,0 +1,268 @@
+// Bitonic network of u32 keys held 32 per lane, every comparator ascending.
+//
+// A wave holds 2^11 keys: element bits 0 .. 4 are the register index, bits
+// 5 .. 10 the lane; above that, bits 11 .. 13 are the wave of a workgroup that
+// sorts up to 2^14 keys. MELD_AUTO uses it where only the sorted order counts,
+// so there is one form, and two things that the paper's forms cannot do:
+//   * no direction anywhere: before phase 2^m the keys of the blocks that
+//     Figure 1 sorts in descending order are complemented, so that every
+//     comparator of the phase is a minimum and a maximum (two operations for two
+//     keys, where a direction per lane takes four); going from one phase to the
+//     next is one exclusive or per key.
+//   * the lane bits never go through LDS. Bits 5 .. 8 are the four DPP
+//     exchanges with lane ^ 1, ^ 2, ^ 7 and ^ 8 (7, a half-row mirror, instead of
+//     4, which would take two moves), and the kept value is the median of the
+//     two and of 0 or ~0: two operations a key. Bits 9 and 10 trade places with
+//     a register bit (v_permlane16/32_swap, half an operation a key), are
+//     compared there and trade back.
+// Bits 11 and up move through LDS, 16 bytes per lane and access.
+//
+// Bound by VALU issue: 92 operations a key for 2^11 keys, 131 for 2^13.
+#pragma once
+
+#include "device_common.h"
+
+namespace meld {
+
+namespace {
+
+constexpr int kWaveE = 32;               // keys per lane
+constexpr uint32_t kWaveTile = 64 * kWaveE;
+
+struct WaveLane {
+    uint32_t id;      // bits 5 .. 10 of the lane's elements
+    uint32_t keep[4];  // 0 where the lane is the lower end of lane bit i, else ~0
+};
+
+__device__ __forceinline__ WaveLane wave_lane() {
+    const uint32_t lane = threadIdx.x & 63;
+    WaveLane w;
+    // lane ^ 7 flips id bit 2 alone: the physical bits 0 and 1 carry id bit 2 too.
+    w.id = lane ^ ((lane & 4) ? 3u : 0u);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w.keep[i] = (uint32_t)-(int32_t)((w.id >> i) & 1u);
+    return w;
+}
+
+// Median of x, y and z: the smaller of x and y for z = 0, the larger for ~0.
+__device__ __forceinline__ uint32_t median(uint32_t x, uint32_t y, uint32_t z) {
+    const uint32_t mn = x < y ? x : y, mx = x < y ? y : x;
+    const uint32_t t = mx < z ? mx : z;
+    return mn > t ? mn : t;
+}
+
+// Register steps on bit Q.
+template <int Q>
+__device__ __forceinline__ void wave_reg_step(uint32_t (&e)[kWaveE]) {
+#pragma unroll
+    for (int r = 0; r < kWaveE; ++r)
+        if ((r & (1 << Q)) == 0) {
+            const uint32_t x = e[r], y = e[r | (1 << Q)];
+            e[r] = x < y ? x : y;
+            e[r | (1 << Q)] = x < y ? y : x;
+        }
+}
+
+// Steps on register bits TOP .. 0.
+template <int TOP>
+__device__ __forceinline__ void wave_reg_steps(uint32_t (&e)[kWaveE]) {
+    if constexpr (TOP >= 0) {
+        wave_reg_step<TOP>(e);
+        wave_reg_steps<TOP - 1>(e);
+    }
+}
+
+// Phases 2^1 .. 2^4: bit M of the register index is the direction.
+template <int M, int Q>
+__device__ __forceinline__ void wave_first_phases(uint32_t (&e)[kWaveE]) {
+    if constexpr (M <= 4) {
+#pragma unroll
+        for (int r = 0; r < kWaveE; ++r)
+            if ((r & (1 << Q)) == 0) {
+                const uint32_t x = e[r], y = e[r | (1 << Q)];
+                const uint32_t mn = x < y ? x : y, mx = x < y ? y : x;
+                e[r] = (r >> M) & 1 ? mx : mn;
+                e[r | (1 << Q)] = (r >> M) & 1 ? mn : mx;
+            }
+        if constexpr (Q > 0)
+            wave_first_phases<M, Q - 1>(e);
+        else
+            wave_first_phases<M + 1, M>(e);
+    }
+}
+
+// The step on lane bit B (element bit 5 + B), B <= 3.
+template <int B>
+__device__ __forceinline__ void wave_lane_step(uint32_t (&e)[kWaveE], uint32_t keep) {
+    constexpr int ctrl = B == 0 ? 0xB1 : B == 1 ? 0x4E : B == 2 ? 0x141 : 0x128;
+#pragma unroll
+    for (int r = 0; r < kWaveE; ++r)
+        e[r] = median(e[r], (uint32_t)__builtin_amdgcn_mov_dpp((int)e[r], ctrl, 0xF, 0xF, true),
+                      keep);
+}
+
+// Trades lane bit 4 (SWAP32: 5) for register bit 4.
+template <bool SWAP32>
+__device__ __forceinline__ void wave_trade(uint32_t (&e)[kWaveE]) {
+#pragma unroll
+    for (int r = 0; r < kWaveE / 2; ++r) {
+        if constexpr (SWAP32) {
+            const auto p = __builtin_amdgcn_permlane32_swap(e[r], e[r + kWaveE / 2], false, false);
+            e[r] = p[0];
+            e[r + kWaveE / 2] = p[1];
+        } else {
+            const auto p = __builtin_amdgcn_permlane16_swap(e[r], e[r + kWaveE / 2], false, false);
+            e[r] = p[0];
+            e[r + kWaveE / 2] = p[1];
+        }
+    }
+}
+
+// Steps on element bits TOP .. 0 of a wave (TOP <= 10). TOP = 10 takes three
+// trades for its two upper bits instead of four and leaves bits 9 and 10 in
+// each other's place: bit 9 is lane bit 5 then, bit 10 lane bit 4.
+template <int TOP>
+__device__ __forceinline__ void wave_steps(uint32_t (&e)[kWaveE], const WaveLane &w) {
+    if constexpr (TOP == 10) {
+        wave_trade<true>(e);
+        wave_reg_step<4>(e);
+        wave_trade<false>(e);
+        wave_reg_step<4>(e);
+        wave_trade<true>(e);
+        wave_steps<8>(e, w);
+    } else if constexpr (TOP == 9) {
+        wave_trade<false>(e);
+        wave_reg_step<4>(e);
+        wave_trade<false>(e);
+        wave_steps<8>(e, w);
+    } else if constexpr (TOP >= 5) {
+        wave_lane_step<TOP - 5>(e, w.keep[TOP - 5]);
+        wave_steps<TOP - 1>(e, w);
+    } else {
+        wave_reg_steps<TOP>(e);
+    }
+}
+
+__device__ __forceinline__ void wave_flip(uint32_t (&e)[kWaveE], uint32_t mask) {
+#pragma unroll
+    for (int r = 0; r < kWaveE; ++r) e[r] ^= mask;
+}
+
+// The complement of phase 2^M of a sort whose last phase is 2^LAST: all ones
+// where bit M of the elements is set, nothing in the last phase. high: bits 5
+// and up of the lane's elements.
+template <int M, int LAST>
+__device__ __forceinline__ uint32_t wave_down(uint32_t high) {
+    return M < LAST ? (uint32_t)-(int32_t)((high >> (M - 5)) & 1u) : 0u;
+}
+
+// Phases 2^M .. 2^min(LAST, 11) on keys already complemented for phase 2^M.
+template <int M, int LAST>
+__device__ __forceinline__ void wave_phases(uint32_t (&e)[kWaveE], const WaveLane &w,
+                                            uint32_t high) {
+    wave_steps<M - 1>(e, w);
+    if constexpr (M < LAST && M < 11) {
+        wave_flip(e, wave_down<M, LAST>(high) ^ wave_down<M + 1, LAST>(high));
+        wave_phases<M + 1, LAST>(e, w, high);
+    }
+}
+
+// Position of a tile's element in LDS: four words of padding per 32, so that
+// the 16-byte accesses of both layouts are free of bank conflicts.
+__device__ __forceinline__ constexpr uint32_t wave_phys(uint32_t i) { return i + (i >> 5) * 4; }
+constexpr uint32_t wave_lds_words(uint32_t tile) { return tile / 32 * 36; }
+
+// The lane's row of 32 elements in LDS, with bits 9 and 10 in each other's
+// place (P) or not.
+template <bool P>
+__device__ __forceinline__ uint32_t *wave_row(uint32_t *s, const WaveLane &w) {
+    const uint32_t id = P ? (w.id & 15u) | ((w.id & 16u) << 1) | ((w.id & 32u) >> 1) : w.id;
+    return s + id * 36;
+}
+
+template <bool P>
+__device__ __forceinline__ void wave_to_lds(const uint32_t (&e)[kWaveE], uint32_t *s,
+                                            const WaveLane &w) {
+    uint4 *row = reinterpret_cast<uint4 *>(wave_row<P>(s, w));
+#pragma unroll
+    for (int c = 0; c < kWaveE / 4; ++c)
+        row[c] = make_uint4(e[4 * c], e[4 * c + 1], e[4 * c + 2], e[4 * c + 3]);
+}
+
+template <bool P>
+__device__ __forceinline__ void wave_from_lds(uint32_t (&e)[kWaveE], uint32_t *s,
+                                              const WaveLane &w) {
+    const uint4 *row = reinterpret_cast<const uint4 *>(wave_row<P>(s, w));
+#pragma unroll
+    for (int c = 0; c < kWaveE / 4; ++c) {
+        const uint4 v = row[c];
+        e[4 * c] = v.x;
+        e[4 * c + 1] = v.y;
+        e[4 * c + 2] = v.z;
+        e[4 * c + 3] = v.w;
+    }
+}
+
+// Steps on element bits TOP .. 11 (TOP <= 13) of a tile of 2^LOG elements
+// whose waves hold 2^11 each: every lane takes 2^(LOG-11) pieces of
+// neighbouring elements, one of each wave's. Bits 9 and 10 are in each other's
+// place on entry, and not on return. s: the workgroup's tile.
+template <int LOG, int TOP>
+__device__ __forceinline__ void wave_cross_steps(uint32_t (&e)[kWaveE], uint32_t *s,
+                                                 const WaveLane &w) {
+    constexpr int WB = LOG - 11;  // wave bits
+    constexpr int GB = 5 - WB;    // low element bits that stay registers
+    const uint32_t wave = threadIdx.x / 64;
+    uint32_t *own = s + wave * wave_lds_words(kWaveTile);
+    wave_to_lds<true>(e, own, w);
+    __syncthreads();
+    // Piece of 2^GB elements number threadIdx.x of every wave's 2^11.
+    uint32_t *p = s + wave_phys((uint32_t)threadIdx.x << GB);
+#pragma unroll
+    for (int r = 0; r < kWaveE; r += 4) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(
+            p + (r >> GB) * wave_lds_words(kWaveTile) + (r & ((1 << GB) - 1)));
+        e[r] = v.x;
+        e[r + 1] = v.y;
+        e[r + 2] = v.z;
+        e[r + 3] = v.w;
+    }
+    if constexpr (TOP >= 13) wave_reg_step<GB + 2>(e);
+    if constexpr (TOP >= 12) wave_reg_step<GB + 1>(e);
+    wave_reg_step<GB>(e);
+#pragma unroll
+    for (int r = 0; r < kWaveE; r += 4)
+        *reinterpret_cast<uint4 *>(p + (r >> GB) * wave_lds_words(kWaveTile) +
+                                   (r & ((1 << GB) - 1))) =
+            make_uint4(e[r], e[r + 1], e[r + 2], e[r + 3]);
+    __syncthreads();
+    wave_from_lds<false>(e, own, w);
+}
+
+// Phases 2^M .. 2^LOG (M >= 12) on keys complemented for phase 2^(M-1).
+template <int M, int LOG>
+__device__ __forceinline__ void wave_cross_phases(uint32_t (&e)[kWaveE], uint32_t *s,
+                                                  const WaveLane &w, uint32_t high) {
+    if constexpr (M <= LOG) {
+        wave_flip(e, wave_down<M - 1, LOG>(high) ^ wave_down<M, LOG>(high));
+        wave_cross_steps<LOG, M - 1>(e, s, w);
+        wave_steps<10>(e, w);
+        wave_cross_phases<M + 1, LOG>(e, s, w, high);
+    }
+}
+
+// Sorts every 2^LOG keys (6 <= LOG <= 14) of the wave, or of the workgroup of
+// 2^(LOG-11) waves, from any order into rows of 32 per lane; bits 9 and 10 are
+// in each other's place for LOG >= 11. s: 2^LOG elements of LDS for LOG >= 12.
+template <int LOG>
+__device__ __forceinline__ void wave_sort(uint32_t (&e)[kWaveE], uint32_t *s, const WaveLane &w) {
+    const uint32_t high = w.id | (LOG > 11 ? threadIdx.x / 64 << 6 : 0u);
+    wave_first_phases<1, 0>(e);
+    wave_flip(e, wave_down<5, LOG>(high));
+    wave_phases<5, LOG>(e, w, high);
+    wave_cross_phases<12, LOG>(e, s, w, high);
+}
+
+}  // namespace
+
+}  // namespace meld
