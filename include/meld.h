@@ -133,8 +133,9 @@ const char *meld_last_error(void);
  * read or written in the caller's arrays.
  * MELD_AUTO runs the network up to 2^15 keys or 2^17 pairs, with
  * MELD_OPT_SORT_LOG_TILE or MELD_OPT_LANE_EXCHANGE set, under capture, and
- * where the scratch below cannot be allocated; otherwise a least-significant-
- * digit radix sort, which gives the same (unique) result in at most four
+ * where the scratch below cannot be allocated, except that without those
+ * options one workgroup sorts 2^11 + 1 .. 2^14 keys in registers; otherwise a
+ * least-significant-digit radix sort, which gives the same (unique) result in at most four
  * passes per word. Its scratch, owned by the context, is as large as the
  * arrays plus at most 1/8 of that for digit counts.
  *
@@ -191,7 +192,8 @@ meld_status meld_sort_u32_steps(meld_ctx *ctx, uint32_t *keys, uint32_t *payload
  * elements (the network of the Motivating Example section, Figure 1, split
  * into on-chip and HBM passes), as JSON in buf (NUL-terminated), without
  * launching anything; "sorts_by" says whether meld_sort_u32 on this context
- * runs this network or, under MELD_AUTO, radix passes ("network", "radix"):
+ * runs this network or, under MELD_AUTO, another sort ("network", "registers",
+ * "radix"):
  *   {"n", "log_n", "pairs", "tuned", "sorts_by", "log_tile", "low", "high",
  *    "hbm_passes", "steps", "passes": [{"kind", "steps", "m", "b_hi", "b_lo"}]}
  * kind "tile" (everything in one tile), "local" (every tile's phases up to
@@ -266,10 +268,14 @@ meld_status meld_oddeven_sort_buckets_u32(meld_ctx *ctx, uint32_t *keys, size_t 
  * run A or of run B, a data-dependent branch: the divergent form runs its two
  * sides (emit, advance, load the next key of that run) as written, the melded
  * form selects the emitted key and issues one load from a selected address.
- * Ties take run A first. MELD_AUTO times both forms once per shape class.
+ * Ties take run A first. MELD_AUTO with all passes sorts as meld_sort_u32 does
+ * (up to 2^14 keys in registers, above by radix passes); with max_passes, under
+ * capture of more than 2^14 keys, and without the memory for the radix scratch
+ * it times both forms once per shape class.
  *
  * keys:    device u32[n], n < 2^31.
- * Scratch: a second buffer of n keys, owned by the context.
+ * Scratch: a second buffer of n keys (MELD_AUTO: at most 9/8 n), owned by the
+ *          context.
  * Errors:  MELD_EINVAL for NULL/host pointers or n >= 2^31. */
 meld_status meld_merge_sort_u32(meld_ctx *ctx, uint32_t *keys, size_t n, int64_t max_passes,
                                 meld_variant variant, void *stream);

@@ -645,6 +645,36 @@ bool radix_sorts(const meld_ctx *ctx, bool pairs, size_t n) {
            n > (pairs ? (size_t)1 << 17 : (size_t)1 << 15);
 }
 
+// Sorts of up to so many keys take one workgroup (bucket_sort.hip).
+constexpr size_t kOneBucket = (size_t)1 << 14;
+
+meld_status sort_one_bucket(uint32_t *keys, size_t n, hipStream_t s) {
+    const uint32_t log_b = std::max(6u, log2_ceil(n));
+    hipError_t e = meld::launch_bucket_sort(keys, (uint32_t)n, log_b, s);
+    return e == hipSuccess ? MELD_OK : hip_fail(e, "bucket sort launch");
+}
+
+// Whether MELD_AUTO sorts n keys in one workgroup: above one wave's 2^11 keys,
+// where the network's tiles need several launches or many barriers (with the
+// copy of the input, bucket against the tuned network, microseconds: 2^11 10.9 /
+// 10.8, 3000 13.0 / 15.0, 2^12 12.0 / 14.8, 2^13 14.3 / 21.2, 2^14 23.9 / 29.3).
+bool bucket_sorts(const meld_ctx *ctx, bool pairs, size_t n) {
+    return !pairs && ctx->sort_log_tile == 0 && ctx->lane_exchange < 0 && n > ((size_t)1 << 11) &&
+           n <= kOneBucket;
+}
+
+// The radix sort on the context's scratch; *done is false where that cannot be
+// allocated.
+meld_status try_radix_sort(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size_t n,
+                           hipStream_t s, bool *done) {
+    *done = ensure_words(&ctx->merge_buf, &ctx->merge_words,
+                         meld::radix_scratch_words((uint32_t)n, payload != nullptr),
+                         "radix scratch") == MELD_OK;
+    if (!*done) return MELD_OK;
+    hipError_t e = meld::launch_radix_sort(keys, payload, (uint32_t)n, ctx->merge_buf, s);
+    return e == hipSuccess ? MELD_OK : hip_fail(e, "radix sort launch");
+}
+
 // Probe of one tile's network: mixed-wave fraction of the phases k <= 64 and
 // k >= 128.
 meld_status probe_network(meld_ctx *ctx, uint32_t log_t, hipStream_t s, double *mixed_lo,
@@ -1204,16 +1234,13 @@ meld_status meld_sort_u32(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size
         return fail(MELD_EINVAL, "meld_sort_u32: payload is not a device pointer on device %d",
                     ctx->device);
     const hipStream_t s = static_cast<hipStream_t>(stream);
+    if (variant == MELD_AUTO && bucket_sorts(ctx, payload != nullptr, n))
+        return sort_one_bucket(keys, n, s);
     if (variant == MELD_AUTO && radix_sorts(ctx, payload != nullptr, n) && !capturing(s)) {
-        // Without the memory for its scratch, the network, which needs less.
-        if (ensure_words(&ctx->merge_buf, &ctx->merge_words,
-                         meld::radix_scratch_words((uint32_t)n, payload != nullptr),
-                         "radix scratch") == MELD_OK) {
-            hipError_t e =
-                meld::launch_radix_sort(keys, payload, (uint32_t)n, ctx->merge_buf, s);
-            if (e != hipSuccess) return hip_fail(e, "radix sort launch");
-            return MELD_OK;
-        }
+        // Without the memory for its scratch, the network, which needs none.
+        bool done = false;
+        meld_status st = try_radix_sort(ctx, keys, payload, n, s, &done);
+        if (done) return st;
     }
     SortPlan plan = fixed_plan(ctx, payload != nullptr, n, variant);
     if (variant == MELD_AUTO) {
@@ -1312,9 +1339,11 @@ meld_status meld_sort_plan_describe(meld_ctx *ctx, size_t n, int with_payload,
     const uint32_t log_n = n <= 1 ? 0 : log2_ceil(n);
     const bool m = variant == MELD_AUTO || use_melded(variant);
     SortPlan plan{default_log_tile(pairs, log_n), m, m, true};
-    bool tuned = false, radix = false;
+    bool tuned = false;
+    const char *by = "network";
     if (ctx != nullptr) {
-        radix = variant == MELD_AUTO && radix_sorts(ctx, pairs, n);
+        if (variant == MELD_AUTO && bucket_sorts(ctx, pairs, n)) by = "registers";
+        if (variant == MELD_AUTO && radix_sorts(ctx, pairs, n)) by = "radix";
         plan.log_t = plan_log_tile(ctx, pairs, log_n);
         plan.xch = plan_xch(ctx);
         if (variant == MELD_AUTO) tuned = cached_sort_plan(ctx, pairs, log_n, &plan);
@@ -1322,7 +1351,7 @@ meld_status meld_sort_plan_describe(meld_ctx *ctx, size_t n, int with_payload,
     std::string d = fmt("{\"n\": %zu, \"log_n\": %u, \"pairs\": %s, \"tuned\": %s, "
                         "\"sorts_by\": \"%s\"",
                         n, log_n, pairs ? "true" : "false", tuned ? "true" : "false",
-                        radix ? "radix" : "network");
+                        by);
     uint32_t hbm = 0, steps = 0;
     std::string list;
     if (n > 1) {
@@ -1402,6 +1431,18 @@ meld_status meld_merge_sort_u32(meld_ctx *ctx, uint32_t *keys, size_t n, int64_t
         return fail(MELD_EINVAL, "%s: keys is not a device pointer on device %d", name,
                     ctx->device);
     const hipStream_t s = static_cast<hipStream_t>(stream);
+    // All passes: only the sorted array counts (with the copy of the input, against
+    // the faster form of the merge sort, microseconds: 1000 keys 10.3 / 17.6, 2^14
+    // 23.9 / 47.5, 2^15 35.6 / 62, 2^20 55 / 135, 2^24 228 / 696). Under capture, and
+    // without the memory for the radix scratch, the merge passes.
+    if (variant == MELD_AUTO && max_passes < 0) {
+        if (n <= kOneBucket) return sort_one_bucket(keys, n, s);
+        bool done = false;
+        if (!capturing(s)) {
+            meld_status st = try_radix_sort(ctx, keys, nullptr, n, s, &done);
+            if (done) return st;
+        }
+    }
     bool melded = use_melded(variant);
     if (variant == MELD_AUTO) {
         auto run = [&](uint32_t *k, bool m) { return merge_sort_impl(ctx, k, n, -1, m, s); };

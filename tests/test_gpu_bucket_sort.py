@@ -57,3 +57,18 @@ def test_zero_one_thresholds(log_b):
         rows[i] = np.roll(rows[i], rng.randint(size)) if i % 2 else rng.permutation(rows[i])
     want = np.sort(rows, axis=1).ravel()
     assert np.array_equal(_sorted(rows.ravel(), log_b, 0), want)
+
+
+@pytest.mark.parametrize("n", [2, 64, 2048, 2049, 5000, 1 << 14, (1 << 14) + 1, 1 << 15,
+                               (1 << 15) + 1, (1 << 19) + 1])
+def test_whole_arrays(n):
+    # The edges of the rules that send MELD_AUTO sorts and merge sorts to one
+    # workgroup, to the network and to radix passes.
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    keys = workloads.keys_u32(n, n)
+    want = oracle.sort_u32(keys)
+    for sort in (meld.sort, meld.merge_sort):
+        k = torch.from_numpy(keys.view(np.int32)).to("cuda:0")
+        sort(k, variant="auto")
+        assert np.array_equal(k.cpu().numpy().view(np.uint32), want), sort.__name__
