@@ -200,6 +200,24 @@ hipError_t launch_segmented_sort(uint32_t *keys, uint32_t n_keys, const uint32_t
                                  uint32_t *work, uint32_t grid, bool meld_lo, bool meld_hi,
                                  bool xch, hipStream_t stream);
 
+// The segmented sort in registers (segsort_auto.hip). All zero before a call; the
+// sort clears `next`, the state of the call after it.
+struct SegAutoState {
+    uint32_t cnt[kSegClasses];   // segments per size class
+    uint32_t fill[kSegClasses];  // scatter cursors
+    uint32_t flag;               // invalid-offset bits of this call
+    uint32_t head;               // next work item
+};
+hipError_t seg_auto_grid(int device, uint32_t *grid);
+// Checks and classes (cls: nseg bytes), with the offsets' end to host memory
+// where total is not NULL; then the sort (queue: nseg words).
+hipError_t launch_segmented_auto_plan(uint32_t n_keys, const uint32_t *off, uint32_t nseg,
+                                      SegAutoState *st, uint32_t *sticky, uint8_t *cls,
+                                      uint32_t *total, hipStream_t stream);
+hipError_t launch_segmented_auto_sort(uint32_t *keys, const uint32_t *off, uint32_t nseg,
+                                      SegAutoState *st, SegAutoState *next, const uint8_t *cls,
+                                      uint32_t *queue, uint32_t grid, hipStream_t stream);
+
 // Batcher's odd-even merge network on each bucket of 2^log_t keys
 // (oddeven.hip; log_t in 6..14, the last bucket ragged), at most max_steps
 // steps per bucket (negative: all), divergent or melded.

@@ -28,6 +28,14 @@ struct meld_ctx {
     size_t seg_cap = 0;  // segments the two arrays above hold
     uint32_t *seg_work = nullptr;
     uint32_t seg_grid = 0;
+    // The segmented sort in registers: its states (two, used in turn), host memory
+    // that receives offsets[nseg], and the event after that write.
+    meld::SegAutoState *seg_auto = nullptr;
+    int seg_auto_turn = 0;
+    uint32_t seg_auto_grid = 0;
+    bool seg_auto_dirty = false;  // new, or a launch failed in between: clear them first
+    uint32_t *seg_total = nullptr;
+    hipEvent_t seg_total_ready = nullptr;
     // Captured segmented-sort sequences (reset, classify, plan, scatter,
     // persistent sort), most recently used first, replayed on the caller's
     // stream. A graph bakes in its arguments, hence the key.
@@ -264,6 +272,66 @@ meld_status ensure_seg(meld_ctx *ctx, size_t nseg) {
     return MELD_OK;
 }
 
+// Offsets are u32, so any key count of 2^32 - 1 or more bounds every offset.
+uint32_t key_bound(size_t n_keys) {
+    return n_keys >= 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)n_keys;
+}
+
+// Scratch of the segmented sort in registers, besides ensure_seg's.
+meld_status ensure_seg_auto(meld_ctx *ctx) {
+    if (ctx->seg_auto == nullptr) {
+        hipError_t e = meld::seg_auto_grid(ctx->device, &ctx->seg_auto_grid);
+        if (e != hipSuccess) return hip_fail(e, "segmented sort occupancy query");
+        meld_status st = dev_alloc(reinterpret_cast<void **>(&ctx->seg_auto),
+                                   2 * sizeof(meld::SegAutoState), "segmented sort state");
+        if (st != MELD_OK) return st;
+        ctx->seg_auto_dirty = true;
+    }
+    if (ctx->seg_total == nullptr &&
+        hipHostMalloc(reinterpret_cast<void **>(&ctx->seg_total), sizeof(uint32_t)) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx->seg_total = nullptr;
+        return fail(MELD_ENOMEM, "cannot allocate pinned host memory");
+    }
+    if (ctx->seg_total_ready == nullptr) {
+        hipError_t e = hipEventCreateWithFlags(&ctx->seg_total_ready, hipEventDisableTiming);
+        if (e != hipSuccess) return hip_fail(e, "hipEventCreate");
+    }
+    return MELD_OK;
+}
+
+// Enqueues the segmented sort in registers. With check, offsets[nseg] comes to
+// the host while the sort runs, and a value beyond n_keys is MELD_EINVAL (the
+// kernels leave the keys untouched then).
+meld_status segmented_auto(meld_ctx *ctx, uint32_t *keys, uint32_t n_keys, const uint32_t *offsets,
+                           uint32_t nseg, bool check, hipStream_t s) {
+    hipError_t e = hipSuccess;
+    if (ctx->seg_auto_dirty)
+        e = meld::launch_fill_u32(reinterpret_cast<uint32_t *>(ctx->seg_auto), 0u,
+                                  2 * sizeof(meld::SegAutoState) / sizeof(uint32_t), s);
+    ctx->seg_auto_dirty = true;
+    meld::SegAutoState *st = ctx->seg_auto + ctx->seg_auto_turn;
+    meld::SegAutoState *next = ctx->seg_auto + (ctx->seg_auto_turn ^ 1);
+    if (e == hipSuccess)
+        e = meld::launch_segmented_auto_plan(n_keys, offsets, nseg, st,
+                                             &ctx->seg_state->sticky, ctx->seg_cls,
+                                             check ? ctx->seg_total : nullptr, s);
+    if (e == hipSuccess && check) e = hipEventRecord(ctx->seg_total_ready, s);
+    if (e == hipSuccess)
+        e = meld::launch_segmented_auto_sort(keys, offsets, nseg, st, next, ctx->seg_cls,
+                                             ctx->seg_queue, ctx->seg_auto_grid, s);
+    if (e != hipSuccess) return hip_fail(e, "segmented sort launch");
+    ctx->seg_auto_turn ^= 1;
+    ctx->seg_auto_dirty = false;
+    if (!check) return MELD_OK;
+    e = hipEventSynchronize(ctx->seg_total_ready);
+    if (e != hipSuccess) return hip_fail(e, "waiting for offsets[nseg]");
+    if (*ctx->seg_total > n_keys)
+        return fail(MELD_EINVAL, "meld_segmented_sort_u32: offsets[nseg] = %u > n_keys = %u",
+                    *ctx->seg_total, n_keys);
+    return MELD_OK;
+}
+
 // The graph of (keys, n_keys, offsets, nseg, forms), captured on first use.
 meld_status seg_graph(meld_ctx *ctx, uint32_t *keys, uint32_t n_keys, const uint32_t *offsets,
                       size_t nseg, bool lo, bool hi, bool xch, hipGraphExec_t *out) {
@@ -302,11 +370,6 @@ meld_status seg_graph(meld_ctx *ctx, uint32_t *keys, uint32_t n_keys, const uint
     ctx->seg_graphs.push_front({keys, offsets, nseg, n_keys, lo, hi, xch, exec});
     *out = exec;
     return MELD_OK;
-}
-
-// Offsets are u32, so any key count of 2^32 - 1 or more bounds every offset.
-uint32_t key_bound(size_t n_keys) {
-    return n_keys >= 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)n_keys;
 }
 
 meld_status segmented_impl(meld_ctx *ctx, uint32_t *keys, size_t n_keys, const uint32_t *offsets,
@@ -849,15 +912,39 @@ meld_status auto_sort_plan(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, siz
     return MELD_OK;
 }
 
+// How MELD_AUTO runs a segmented sort: the network's forms, or in registers.
+struct SegPlan {
+    bool lo, hi, xch;
+    bool in_registers;
+};
+
+// The tuner's decision for a shape class of the segmented sort. The key names
+// the candidates (r: the sort in registers among them), so that a decision
+// made without it is not taken for one made with it.
+std::string seg_tune_key(const meld_ctx *ctx, size_t nseg, size_t n_keys) {
+    std::string key = fmt("nseg=%u keys=%u r", log2_ceil(nseg), log2_ceil(n_keys));
+    if (ctx->lane_exchange >= 0)
+        key = fmt("nseg=%u keys=%u x=%d", log2_ceil(nseg), log2_ceil(n_keys), ctx->lane_exchange);
+    return key;
+}
+
+bool cached_seg_plan(const meld_ctx *ctx, size_t nseg, size_t n_keys, SegPlan *out) {
+    const meld::TuneEntry *t = ctx->tuner.find("segsort", seg_tune_key(ctx, nseg, n_keys));
+    if (t == nullptr) return false;
+    *out = SegPlan{t->lo != 0, t->hi != 0, t->xch == 1, t->xch == 2};
+    return true;
+}
+
 // MELD_AUTO for a segmented sort: the tuned forms of this shape class, timing
-// the four per-stage combinations on a scratch copy the first time.
-meld_status auto_seg_forms(meld_ctx *ctx, uint32_t *keys, size_t n_keys, const uint32_t *offsets,
-                           size_t nseg, hipStream_t s, bool *lo, bool *hi, bool *xch) {
-    *lo = *hi = true;
-    *xch = plan_xch(ctx);
-    if (capturing(s)) {
-        return MELD_OK;
-    }
+// the per-stage combinations on each low-phase path, and the sort in registers,
+// on a scratch copy the first time. An option that fixes the low-phase path asks
+// for the network.
+meld_status auto_seg_plan(meld_ctx *ctx, uint32_t *keys, size_t n_keys, const uint32_t *offsets,
+                          size_t nseg, hipStream_t s, SegPlan *out) {
+    *out = SegPlan{true, true, plan_xch(ctx), false};
+    if (capturing(s)) return MELD_OK;
+    const bool known = cached_seg_plan(ctx, nseg, n_keys, out);
+    if (known && out->in_registers) return MELD_OK;  // which reads offsets[nseg] itself
     uint32_t total = 0;
     hipError_t e = hipMemcpyAsync(&total, offsets + nseg, sizeof total, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -866,25 +953,21 @@ meld_status auto_seg_forms(meld_ctx *ctx, uint32_t *keys, size_t n_keys, const u
     if (total > n_keys)
         return fail(MELD_EINVAL, "meld_segmented_sort_u32: offsets[nseg] = %u > n_keys = %zu",
                     total, n_keys);
-    std::string key = fmt("nseg=%u total=%u", log2_ceil(nseg), log2_ceil(total));
-    if (ctx->lane_exchange >= 0) key += fmt(" x=%d", ctx->lane_exchange);
-    if (const meld::TuneEntry *t = ctx->tuner.find("segsort", key)) {
-        *lo = t->lo != 0;
-        *hi = t->hi != 0;
-        *xch = t->xch != 0;
-        return MELD_OK;
-    }
-    if (total == 0) return MELD_OK;
+    if (known || total == 0) return MELD_OK;
     meld_status st = ensure_words(&ctx->tune_buf, &ctx->tune_words, total, "tuning scratch");
     if (st != MELD_OK) return st;
     st = ensure_seg(ctx, nseg);
     if (st != MELD_OK) return st;
+    std::vector<SegPlan> plans;
+    for (int x = 0; x < 2; ++x)
+        for (int f = 0; f < 4; ++f)
+            if (ctx->lane_exchange < 0 || ctx->lane_exchange == x)
+                plans.push_back(SegPlan{(f & 1) != 0, (f & 2) != 0, x != 0, false});
+    if (ctx->lane_exchange < 0 && ensure_seg_auto(ctx) == MELD_OK)
+        plans.push_back(SegPlan{true, true, true, true});
     std::vector<double> ms;
-    std::vector<int> flo, fhi, fx;
-    const int paths = ctx->lane_exchange >= 0 ? 1 : 2;
-    for (int f = 0; f < 4 * paths; ++f) {
-        const bool l = (f & 1) != 0, h = (f & 2) != 0;
-        const bool x = ctx->lane_exchange >= 0 ? ctx->lane_exchange != 0 : (f & 4) != 0;
+    std::vector<int> flo, fhi;
+    for (const SegPlan &p : plans) {
         double t = 0;
         st = time_median(
             s, 3,
@@ -894,37 +977,37 @@ meld_status auto_seg_forms(meld_ctx *ctx, uint32_t *keys, size_t n_keys, const u
                 return r == hipSuccess ? MELD_OK : hip_fail(r, "tuning copy");
             },
             [&]() -> meld_status {
+                if (p.in_registers)
+                    return segmented_auto(ctx, ctx->tune_buf, total, offsets, (uint32_t)nseg,
+                                          false, s);
                 hipError_t r = meld::launch_segmented_sort(
                     ctx->tune_buf, total, offsets, (uint32_t)nseg, ctx->seg_state, ctx->seg_cls,
-                    ctx->seg_queue, ctx->seg_work, ctx->seg_grid, l, h, x, s);
+                    ctx->seg_queue, ctx->seg_work, ctx->seg_grid, p.lo, p.hi, p.xch, s);
                 return r == hipSuccess ? MELD_OK : hip_fail(r, "segmented sort launch");
             },
             &t);
         if (st != MELD_OK) return st;
         ms.push_back(t);
-        flo.push_back(l);
-        fhi.push_back(h);
-        fx.push_back(x);
+        flo.push_back(p.lo);
+        fhi.push_back(p.hi);
     }
     unsigned long long c[4] = {0};
-    st = run_probe(ctx, s, 4, c, [&](unsigned long long *out) {
-        return meld::launch_probe_segments(offsets, (uint32_t)nseg, out, s);
+    st = run_probe(ctx, s, 4, c, [&](unsigned long long *o) {
+        return meld::launch_probe_segments(offsets, (uint32_t)nseg, o, s);
     });
     if (st != MELD_OK) return st;
     const double mixed_lo = c[1] ? (double)c[0] / (double)c[1] : 0.0;
     const double mixed_hi = c[3] ? (double)c[2] / (double)c[3] : 0.0;
     const int pick = meld::choose((int)ms.size(), ms.data(), flo.data(), fhi.data(), mixed_lo,
                                   mixed_hi, ctx->theta, ctx->tie);
-    *lo = flo[pick] != 0;
-    *hi = fhi[pick] != 0;
-    *xch = fx[pick] != 0;
+    *out = plans[pick];
     meld::TuneEntry te;
     te.op = "segsort";
-    te.key = key;
-    te.lo = *lo;
-    te.hi = *hi;
-    te.xch = *xch;
-    te.form = *lo ? 1 : 0;
+    te.key = seg_tune_key(ctx, nseg, n_keys);
+    te.lo = out->lo;
+    te.hi = out->hi;
+    te.xch = out->in_registers ? 2 : out->xch ? 1 : 0;
+    te.form = out->lo ? 1 : 0;
     te.ms = ms[pick];
     te.mixed_lo = mixed_lo;
     te.mixed_hi = mixed_hi;
@@ -1215,8 +1298,11 @@ void meld_destroy(meld_ctx *ctx) {
     if (ctx->capture_stream != nullptr) (void)hipStreamDestroy(ctx->capture_stream);
     for (void *p : {(void *)ctx->seg_state, (void *)ctx->seg_cls,
                     (void *)ctx->seg_queue, (void *)ctx->seg_work, (void *)ctx->tune_buf,
-                    (void *)ctx->merge_buf, (void *)ctx->merge_cuts, (void *)ctx->probe_buf})
+                    (void *)ctx->merge_buf, (void *)ctx->merge_cuts, (void *)ctx->probe_buf,
+                    (void *)ctx->seg_auto})
         if (p != nullptr) (void)hipFree(p);
+    if (ctx->seg_total != nullptr) (void)hipHostFree(ctx->seg_total);
+    if (ctx->seg_total_ready != nullptr) (void)hipEventDestroy(ctx->seg_total_ready);
     delete ctx;
 }
 
@@ -1579,8 +1665,18 @@ meld_status meld_segmented_sort_u32(meld_ctx *ctx, uint32_t *keys, size_t n_keys
                         "meld_segmented_sort_u32: keys and offsets must be device pointers on "
                         "device %d",
                         ctx->device);
-        meld_status st = auto_seg_forms(ctx, keys, n_keys, offsets, nseg, s, &lo, &hi, &xch);
+        SegPlan plan;
+        meld_status st = auto_seg_plan(ctx, keys, n_keys, offsets, nseg, s, &plan);
         if (st != MELD_OK) return st;
+        if (plan.in_registers) {
+            st = ensure_seg(ctx, nseg);
+            if (st == MELD_OK) st = ensure_seg_auto(ctx);
+            if (st != MELD_OK) return st;
+            return segmented_auto(ctx, keys, key_bound(n_keys), offsets, (uint32_t)nseg, true, s);
+        }
+        lo = plan.lo;
+        hi = plan.hi;
+        xch = plan.xch;
     }
     return segmented_impl(ctx, keys, n_keys, offsets, nseg, lo, hi, xch, s,
                           "meld_segmented_sort_u32");

@@ -168,7 +168,8 @@ __device__ __forceinline__ void wave_phases(uint32_t (&e)[kWaveE], const WaveLan
 }
 
 // Position of a tile's element in LDS: four words of padding per 32, so that
-// the 16-byte accesses of both layouts are free of bank conflicts.
+// the 16-byte accesses of both layouts are free of bank conflicts. For b a
+// multiple of 32, wave_phys(a + b) = wave_phys(a) + wave_phys(b).
 __device__ __forceinline__ constexpr uint32_t wave_phys(uint32_t i) { return i + (i >> 5) * 4; }
 constexpr uint32_t wave_lds_words(uint32_t tile) { return tile / 32 * 36; }
 
