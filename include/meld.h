@@ -222,11 +222,13 @@ meld_status meld_sort_plan_describe(meld_ctx *ctx, size_t n, int with_payload,
  * offsets: device u32[nseg + 1], offsets[0] = 0, non-decreasing. Segments
  *          may be empty. Segment length <= 65536.
  * nseg:    number of segments, < 2^31; 0 is a no-op.
- * Runs as one persistent launch after three small planning kernels that
- * build a largest-first work queue on the device; nothing is read back to
- * the host. Scratch: 5 bytes per segment plus 256 KiB per resident
- * workgroup (one per CU) for staging segments of more than 2^14 keys, owned
- * by the context.
+ * Runs as one persistent launch after two or three small planning kernels
+ * that build a largest-first work queue on the device; the explicit forms read
+ * nothing back to the host. MELD_AUTO also times a sort of all comparators in
+ * ascending order in registers, which gives the same (unique) result, and runs
+ * the faster. Scratch: 5 bytes per segment plus 256 KiB per resident workgroup
+ * (one per CU) for staging segments of more than 2^14 keys, owned by the
+ * context.
  * Errors:  MELD_EINVAL for NULL/host pointers. Offsets live on the device
  *          and are not inspected on the host: a segment longer than 65536,
  *          decreasing offsets, offsets[0] != 0 or an offset above n_keys

@@ -17,6 +17,8 @@
 // chunk in registers. The direction of a chunk is bit p of i ^ (len - 1), so that
 // the segment's end ascends in every phase, its padding stays past len and no
 // chunk without keys is ever touched.
+#include <type_traits>
+
 #include "kernels.h"
 #include "wave_network.h"
 
@@ -180,13 +182,21 @@ __device__ __forceinline__ void sa_cross_phases(uint32_t (&e)[kWaveE], uint32_t 
     }
 }
 
+// Where the keys of a tile or of a wave's part of one go: a segment of len keys
+// at lo, per lane; or, whole, a tile of 2^14 keys that all exist, at an lo that is
+// the workgroup's: then no access needs a check, and all of them share one
+// scalar base (checked, an access takes three to five VALU operations).
+struct SaPlace {
+    uint32_t lo, len;
+    bool whole;
+};
+
 // Writes the wave's sorted rows to the caller's keys: position i of the wave's
-// 2^11 is key (first + i) mod 2^c of the segment of the lanes that hold it (lo,
-// len: the lane's segment), if it has one. P: bits 9 and 10 are in each other's
-// place.
+// 2^11 is key (first + i) mod 2^c of the segment of the lanes that hold it, if it
+// has one. traded: bits 9 and 10 are in each other's place.
 __device__ __forceinline__ void sa_store(const uint32_t (&e)[kWaveE], uint32_t *own,
                                          const WaveLane &w, uint32_t *__restrict__ keys,
-                                         uint32_t lo, uint32_t len, uint32_t c, uint32_t first,
+                                         const SaPlace &at, uint32_t c, uint32_t first,
                                          bool traded, uint32_t flip) {
     if (traded)
         wave_to_lds<true>(e, own, w);
@@ -194,122 +204,36 @@ __device__ __forceinline__ void sa_store(const uint32_t (&e)[kWaveE], uint32_t *
         wave_to_lds<false>(e, own, w);
     __builtin_amdgcn_wave_barrier();
     uint32_t lane = threadIdx.x & 63;
+    if (at.whole) {
+        uint32_t *k = keys + scalar(at.lo) + scalar(first);
 #pragma unroll
-    for (int r = 0; r < kWaveE; ++r) {
-        opaque(lane);
-        const uint32_t i = r * 64;
-        // Lanes of the wave by element order, one per 32 positions.
-        const uint32_t id = c < kSaTopWaveClass ? i >> c << (c - 5) : 0u;
-        const int src = (int)(id ^ ((id & 4) ? 3u : 0u));
-        const uint32_t slo = (uint32_t)__builtin_amdgcn_readlane((int)lo, src);
-        const uint32_t slen = (uint32_t)__builtin_amdgcn_readlane((int)len, src);
-        const uint32_t p = (first + i + lane) & ((1u << c) - 1);
-        if (p < slen) key_at(keys + slo, p) = own[wave_phys(lane) + wave_phys(i)] ^ flip;
+        for (int r = 0; r < kWaveE; ++r)
+            key_at(k + r * 64, lane) = own[wave_phys(lane) + wave_phys(r * 64)] ^ flip;
+    } else {
+#pragma unroll
+        for (int r = 0; r < kWaveE; ++r) {
+            opaque(lane);
+            const uint32_t i = r * 64;
+            // Lanes of the wave by element order, one per 32 positions.
+            const uint32_t id = c < kSaTopWaveClass ? i >> c << (c - 5) : 0u;
+            const int src = (int)(id ^ ((id & 4) ? 3u : 0u));
+            const uint32_t slo = (uint32_t)__builtin_amdgcn_readlane((int)at.lo, src);
+            const uint32_t slen = (uint32_t)__builtin_amdgcn_readlane((int)at.len, src);
+            const uint32_t p = (first + i + lane) & ((1u << c) - 1);
+            if (p < slen) key_at(keys + slo, p) = own[wave_phys(lane) + wave_phys(i)] ^ flip;
+        }
     }
     __builtin_amdgcn_wave_barrier();
 }
 
-// Sorts the segment of len <= 2^c keys at keys + lo by the 2^(c-5) lanes that
-// share it (6 <= c <= 14); id numbers the lanes by element order, in the wave for
-// c <= 11, in the workgroup above, where all eight waves take part. With flip =
-// ~0 in descending order (2^c keys, no padding).
-__device__ __forceinline__ void sa_sort(uint32_t *__restrict__ keys, uint32_t lo, uint32_t len,
-                                        uint32_t c, uint32_t id, uint32_t flip, uint32_t *s,
-                                        const WaveLane &w) {
-    const uint32_t log_lanes = c - 5;
-    uint32_t p = id & ((1u << log_lanes) - 1);
-    uint32_t *k = keys + lo;
-    uint32_t e[kWaveE];
+// Keys b + r * 512 + thread of a segment, padding past its end.
+__device__ __forceinline__ void sa_load_rows(uint32_t (&e)[kWaveE], uint32_t *__restrict__ k,
+                                             uint32_t b, uint32_t len) {
+    if (b + kSaTile <= len) {
 #pragma unroll
-    for (int r = 0; r < kWaveE; ++r) {
-        e[r] = kSaPad;
-        if (p < len) e[r] = key_at(k, p);
-        p += 1u << log_lanes;
-        opaque(p);  // one address at a time
-    }
-    if (flip != 0) wave_flip(e, ~0u);
-    wave_first_phases<1, 0>(e);
-    wave_flip(e, wave_down<5, 16>(id));
-    sa_wave_phases<5>(e, w, id, c);
-    sa_cross_phases<12>(e, s, w, id, c);
-    uint32_t *own = s + threadIdx.x / 64 * wave_lds_words(kWaveTile);
-    sa_store(e, own, w, keys, lo, len, c, (id & ~63u) * 32, c >= kSaTopWaveClass, flip);
-}
-
-// Steps j = 2^13 .. 1 on a chunk held as element r * 512 + thread, then its
-// store at keys + lo as far as it is below len.
-__device__ __forceinline__ void sa_merge(uint32_t (&e)[kWaveE], uint32_t *__restrict__ keys,
-                                         uint32_t lo, uint32_t len, uint32_t flip, uint32_t *s,
-                                         const WaveLane &w) {
-    uint32_t t = threadIdx.x;
-    opaque(t);
-    wave_reg_steps<4>(e);
-    __syncthreads();  // every wave has read its rows of the last tile
-#pragma unroll
-    for (int r = 0; r < kWaveE; ++r) s[wave_phys(t) + wave_phys(r * kSaThreads)] = e[r];
-    __syncthreads();
-    uint32_t *own = s + t / 64 * wave_lds_words(kWaveTile);
-    wave_from_lds<false>(e, own, w);
-    wave_steps<8>(e, w);
-    sa_store(e, own, w, keys, lo, len, kSaLogTile, (t & ~63u) * 32, false, flip);
-}
-
-// Phase 2^P (15 or 16) on the block of 2^(P-14) chunks at position b of the
-// segment of len keys at keys + lo: the first chunk's keys stay in registers, the
-// others' go back to memory after the steps across chunks.
-template <int P>
-__device__ __forceinline__ void sa_phase(uint32_t *__restrict__ keys, uint32_t lo, uint32_t len,
-                                         uint32_t b, uint32_t *s, const WaveLane &w) {
-    constexpr uint32_t G = 1u << (P - kSaLogTile);
-    if (b + G / 2 * kSaTile >= len) return;  // one half alone: ascending already
-    const uint32_t flip = (uint32_t)-(int32_t)(((b ^ (len - 1)) >> P) & 1u);
-    uint32_t *k = keys + lo;
-    uint32_t e[kWaveE];
-    __syncthreads();  // the stores of the last phase are visible to the workgroup
-    uint32_t p = b + threadIdx.x;
-    opaque(p);
-    constexpr int R = 32 / G;  // rows in flight
-#pragma unroll
-    for (int r0 = 0; r0 < kWaveE; r0 += R) {
-        uint32_t v[R][G];
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (uint32_t q = 0; q < G; ++q) {
-                const uint32_t i = p + r * kSaThreads + q * kSaTile;
-                v[r][q] = kSaPad;
-                if (i < len) v[r][q] = key_at(k, i);
-            }
-        opaque(p);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-#pragma unroll
-            for (uint32_t q = 0; q < G; ++q) v[r][q] ^= flip;
-#pragma unroll
-            for (uint32_t j = G / 2; j >= 1; j /= 2)
-#pragma unroll
-                for (uint32_t q = 0; q < G; ++q)
-                    if ((q & j) == 0) {
-                        const uint32_t x = v[r][q], y = v[r][q | j];
-                        v[r][q] = x < y ? x : y;
-                        v[r][q | j] = x < y ? y : x;
-                    }
-            e[r0 + r] = v[r][0];
-#pragma unroll
-            for (uint32_t q = 1; q < G; ++q) {
-                const uint32_t i = p + r * kSaThreads + q * kSaTile;
-                if (i < len) key_at(k, i) = v[r][q];
-            }
-        }
-        p += R * kSaThreads;
-        opaque(p);
-    }
-#pragma unroll 1
-    for (uint32_t q = 0;;) {
-        const uint32_t at = b + q * kSaTile;
-        sa_merge(e, keys, lo + at, len - at, flip, s, w);
-        if (++q == G || b + q * kSaTile >= len) break;
-        p = b + q * kSaTile + threadIdx.x;
+        for (int r = 0; r < kWaveE; ++r) e[r] = key_at(k + b + r * kSaThreads, threadIdx.x);
+    } else {
+        uint32_t p = b + threadIdx.x;
         opaque(p);
 #pragma unroll
         for (int r = 0; r < kWaveE; ++r) {
@@ -321,23 +245,188 @@ __device__ __forceinline__ void sa_phase(uint32_t *__restrict__ keys, uint32_t l
     }
 }
 
-__device__ __forceinline__ void sa_chunked(uint32_t *__restrict__ keys, uint32_t lo, uint32_t len,
-                                           uint32_t c, uint32_t *s, const WaveLane &w) {
-    const uint32_t id = (threadIdx.x & ~63u) | w.id;
-#pragma unroll 1
-    for (uint32_t b = 0; b < len; b += kSaTile) {
-        const uint32_t flip = (uint32_t)-(int32_t)(((b ^ (len - 1)) >> kSaLogTile) & 1u);
-        __syncthreads();
-        sa_sort(keys, lo + b, len - b < kSaTile ? len - b : kSaTile, kSaLogTile, id, flip, s, w);
+// The keys of the lane's segment, at most 2^c shared by 2^(c-5) lanes, in any
+// order; id as for sa_sort.
+__device__ __forceinline__ void sa_load(uint32_t (&e)[kWaveE], uint32_t *__restrict__ keys,
+                                        uint32_t lo, uint32_t len, uint32_t c, uint32_t id) {
+    const uint32_t log_lanes = c - 5;
+    uint32_t p = id & ((1u << log_lanes) - 1);
+    uint32_t *k = keys + lo;
+#pragma unroll
+    for (int r = 0; r < kWaveE; ++r) {
+        e[r] = kSaPad;
+        if (p < len) e[r] = key_at(k, p);
+        p += 1u << log_lanes;
+        opaque(p);  // one address at a time
     }
+}
+
+// Sorts the keys loaded for the segment of at most 2^c keys of the 2^(c-5) lanes
+// that share it (6 <= c <= 14) and stores them; id numbers the lanes by element
+// order, in the wave for c <= 11, in the workgroup above, where all eight waves
+// take part. With flip = ~0 in descending order (a whole tile).
+__device__ __forceinline__ void sa_sort(uint32_t (&e)[kWaveE], uint32_t *__restrict__ keys,
+                                        const SaPlace &at, uint32_t c, uint32_t id, uint32_t flip,
+                                        uint32_t *s, const WaveLane &w) {
+    if (flip != 0) wave_flip(e, ~0u);
+    wave_first_phases<1, 0>(e);
+    wave_flip(e, wave_down<5, 16>(id));
+    sa_wave_phases<5>(e, w, id, c);
+    sa_cross_phases<12>(e, s, w, id, c);
+    uint32_t *own = s + threadIdx.x / 64 * wave_lds_words(kWaveTile);
+    sa_store(e, own, w, keys, at, c, (id & ~63u) * 32, c >= kSaTopWaveClass, flip);
+}
+
+// Steps j = 2^13 .. 1 on a chunk held as element r * 512 + thread, then its
+// store.
+__device__ __forceinline__ void sa_merge(uint32_t (&e)[kWaveE], uint32_t *__restrict__ keys,
+                                         const SaPlace &at, uint32_t flip, uint32_t *s,
+                                         const WaveLane &w) {
+    uint32_t t = threadIdx.x;
+    opaque(t);
+    wave_reg_steps<4>(e);
+    __syncthreads();  // every wave has read its rows of the last tile
+#pragma unroll
+    for (int r = 0; r < kWaveE; ++r) s[wave_phys(t) + wave_phys(r * kSaThreads)] = e[r];
+    __syncthreads();
+    uint32_t *own = s + t / 64 * wave_lds_words(kWaveTile);
+    wave_from_lds<false>(e, own, w);
+    wave_steps<8>(e, w);
+    sa_store(e, own, w, keys, at, kSaLogTile, (t & ~63u) * 32, false, flip);
+}
+
+// Phase 2^P (15 or 16) on the block of 2^(P-14) chunks at position b of the
+// segment of len keys at keys + lo: the first chunk's keys stay in registers, the
+// others' go back to memory after the steps across chunks; each is read again
+// while the one before it is merged.
+template <int P>
+__device__ __forceinline__ void sa_phase(uint32_t *__restrict__ keys, uint32_t lo, uint32_t len,
+                                         uint32_t b, uint32_t *s, const WaveLane &w) {
+    constexpr uint32_t G = 1u << (P - kSaLogTile);
+    if (b + G / 2 * kSaTile >= len) return;  // one half alone: ascending already
+    const uint32_t flip = (uint32_t)-(int32_t)(((b ^ (len - 1)) >> P) & 1u);
+    uint32_t *k = keys + lo;
+    uint32_t e[kWaveE];
+    __syncthreads();  // the stores of the last phase are visible to the workgroup
+    constexpr int R = 32 / G;  // rows in flight
+    auto cross = [&](auto whole) {
+        constexpr bool WHOLE = decltype(whole)::value;
+        uint32_t p = b + threadIdx.x;
+        if (!WHOLE) opaque(p);
+#pragma unroll
+        for (int r0 = 0; r0 < kWaveE; r0 += R) {
+            uint32_t v[R][G];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (uint32_t q = 0; q < G; ++q) {
+                    if (WHOLE) {
+                        v[r][q] = key_at(k + b + q * kSaTile + (r0 + r) * kSaThreads, threadIdx.x);
+                    } else {
+                        const uint32_t i = p + r * kSaThreads + q * kSaTile;
+                        v[r][q] = kSaPad;
+                        if (i < len) v[r][q] = key_at(k, i);
+                    }
+                }
+            if (!WHOLE) opaque(p);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+#pragma unroll
+                for (uint32_t q = 0; q < G; ++q) v[r][q] ^= flip;
+#pragma unroll
+                for (uint32_t j = G / 2; j >= 1; j /= 2)
+#pragma unroll
+                    for (uint32_t q = 0; q < G; ++q)
+                        if ((q & j) == 0) {
+                            const uint32_t x = v[r][q], y = v[r][q | j];
+                            v[r][q] = x < y ? x : y;
+                            v[r][q | j] = x < y ? y : x;
+                        }
+                e[r0 + r] = v[r][0];
+#pragma unroll
+                for (uint32_t q = 1; q < G; ++q) {
+                    if (WHOLE) {
+                        key_at(k + b + q * kSaTile + (r0 + r) * kSaThreads, threadIdx.x) = v[r][q];
+                    } else {
+                        const uint32_t i = p + r * kSaThreads + q * kSaTile;
+                        if (i < len) key_at(k, i) = v[r][q];
+                    }
+                }
+            }
+            p += R * kSaThreads;
+            if (!WHOLE) opaque(p);
+        }
+    };
+    if (b + G * kSaTile <= len)
+        cross(std::true_type{});
+    else
+        cross(std::false_type{});
 #pragma unroll 1
-    for (uint32_t b = 0; b < len; b += 2 * kSaTile) sa_phase<15>(keys, lo, len, b, s, w);
+    for (uint32_t q = 0;;) {
+        const uint32_t at = b + q * kSaTile;
+        const bool more = ++q < G && at + kSaTile < len;
+        uint32_t f[kWaveE];
+        if (more) sa_load_rows(f, k, at + kSaTile, len);
+        sa_merge(e, keys, SaPlace{lo + at, len - at, at + kSaTile <= len}, flip, s, w);
+        if (!more) break;
+#pragma unroll
+        for (int r = 0; r < kWaveE; ++r) e[r] = f[r];
+    }
+}
+
+// A work item of a workgroup: class c >= 12, number k of the class.
+__device__ __forceinline__ void sa_big_item(uint32_t *__restrict__ keys,
+                                            const uint32_t *__restrict__ off,
+                                            const uint32_t *__restrict__ queue, const SaPlan &plan,
+                                            uint32_t c, uint32_t k, uint32_t *s,
+                                            const WaveLane &w) {
+    const uint32_t id = (threadIdx.x & ~63u) | w.id;
+    const uint32_t cc = c < kSaLogTile ? c : kSaLogTile;
+    const uint32_t q = (k << (kSaLogTile - cc)) + (id >> (cc - 5));
+    uint32_t lo = 0, len = 0;  // lanes past the class's last segment idle
+    if (q < plan.cnt[c]) {
+        const uint32_t seg = queue[plan.base[c] + q];
+        lo = off[seg];
+        len = off[seg + 1] - lo;
+    }
+    uint32_t e[kWaveE];
+    if (c >= kSaLogTile) {  // one segment
+        lo = scalar(lo);
+        len = scalar(len);
+        sa_load_rows(e, keys + lo, 0, len);
+    } else {
+        sa_load(e, keys, lo, len, c, id);
+    }
+    uint32_t b = 0;
+#pragma unroll 1
+    for (;;) {
+        const bool more = c > kSaLogTile && b + kSaTile < len;
+        uint32_t f[kWaveE];
+        if (more) sa_load_rows(f, keys + lo, b + kSaTile, len);  // while this chunk is sorted
+        SaPlace at{lo + b, len - b, false};
+        uint32_t flip = 0;
+        if (c >= kSaLogTile) {
+            at.whole = b + kSaTile <= len;
+            flip = (uint32_t)-(int32_t)(((b ^ (len - 1)) >> kSaLogTile) & 1u);
+        }
+        sa_sort(e, keys, at, cc, id, flip, s, w);
+        if (!more) break;
+        b += kSaTile;
+#pragma unroll
+        for (int r = 0; r < kWaveE; ++r) e[r] = f[r];
+    }
+    if (c <= kSaLogTile) return;
+#pragma unroll 1
+    for (b = 0; b < len; b += 2 * kSaTile) sa_phase<15>(keys, lo, len, b, s, w);
     if (c > 15) sa_phase<16>(keys, lo, len, 0, s, w);
 }
 
-// Two workgroups of eight waves per CU (72 KiB of LDS each). Bound by VALU issue
-// on large segments (about 150 operations a key of a 2^14-key chunk, 20 more per
-// phase above).
+// Two workgroups of eight waves per CU (72 KiB of LDS each). 4096 segments of
+// log-uniform length in [2^6, 2^16], 3.9e7 keys: 315 us (the network's kernel: 500).
+// 2048 segments of 2^14 keys run at the rate of VALU issue (157 operations a key);
+// at 2^16 keys the two phases across chunks, 50 more operations, wait for the
+// memory half of their time, and the last segments of 2^15 keys leave the chip
+// partly idle.
 __global__ __launch_bounds__(kSaThreads, 4) void sa_sort_kernel(uint32_t *__restrict__ keys,
                                                                 const uint32_t *__restrict__ off,
                                                                 const uint32_t *__restrict__ queue,
@@ -350,29 +439,15 @@ __global__ __launch_bounds__(kSaThreads, 4) void sa_sort_kernel(uint32_t *__rest
     sa_plan(st, plan);
     if (blockIdx.x == 0 && tid < sizeof(SegAutoState) / 4) reinterpret_cast<uint32_t *>(next)[tid] = 0;
     if (plan.flag == 0) {  // otherwise invalid offsets: leave the keys untouched
-        while (plan.big != 0) {
-            if (tid == 0) plan.item = atomicAdd(&st->head, 1u);
-            __syncthreads();
-            const uint32_t item = plan.item;
-            __syncthreads();
-            if (item >= plan.big) break;  // every workgroup reaches this
+        // The first item is the workgroup's own number, later ones come from the
+        // counter when it is done: largest first, whoever is free.
+        for (uint32_t item = blockIdx.x; item < plan.big;) {
             const uint32_t c = sa_class_of(plan, item, kSegClasses - 1, kSaTopWaveClass + 1);
-            const uint32_t k = item - plan.first[c];
-            if (c > kSaLogTile) {
-                const uint32_t seg = queue[plan.base[c] + k];
-                const uint32_t lo = scalar(off[seg]);
-                sa_chunked(keys, lo, scalar(off[seg + 1]) - lo, c, s, w);
-            } else {
-                const uint32_t id = (tid & ~63u) | w.id;
-                const uint32_t q = (k << (kSaLogTile - c)) + (id >> (c - 5));
-                uint32_t lo = 0, len = 0;  // lanes past the class's last segment idle
-                if (q < plan.cnt[c]) {
-                    const uint32_t seg = queue[plan.base[c] + q];
-                    lo = off[seg];
-                    len = off[seg + 1] - lo;
-                }
-                sa_sort(keys, lo, len, c, id, 0, s, w);
-            }
+            sa_big_item(keys, off, queue, plan, c, item - plan.first[c], s, w);
+            __syncthreads();
+            if (tid == 0) plan.item = gridDim.x + atomicAdd(&st->head, 1u);
+            __syncthreads();
+            item = scalar(plan.item);
         }
         // Neighbouring items go to different CUs.
         for (uint32_t item = scalar(tid / 64 * gridDim.x + blockIdx.x); item < plan.small;
@@ -385,7 +460,9 @@ __global__ __launch_bounds__(kSaThreads, 4) void sa_sort_kernel(uint32_t *__rest
                 lo = off[seg];
                 len = off[seg + 1] - lo;
             }
-            sa_sort(keys, lo, len, c, w.id, 0, s, w);
+            uint32_t e[kWaveE];
+            sa_load(e, keys, lo, len, c, w.id);
+            sa_sort(e, keys, SaPlace{lo, len, false}, c, w.id, 0, s, w);
         }
     }
 }
