@@ -149,7 +149,11 @@ def _stream_handle(device: int, stream) -> int:
     current torch stream of ``device``) as an integer."""
     if stream is None:
         import torch
-        stream = torch.cuda.current_stream(device)
+        if not torch.cuda.is_initialized():
+            torch.cuda.init()
+        # The handle alone: building the Stream object takes 1 us of a 6 us call.
+        return torch._C._cuda_getCurrentRawStream(
+            torch.cuda.current_device() if device is None else device)
     return int(stream.cuda_stream if hasattr(stream, "cuda_stream") else stream)
 
 
@@ -172,6 +176,9 @@ def context(device: int, stream=None):
     """The library context of (``device``, ``stream``), created on first use; stream
     None is the current torch stream of the device."""
     key = (device, _stream_handle(device, stream))
+    ctx = _ctxs.get(key)
+    if ctx is not None:
+        return ctx
     with _lock:
         ctx = _ctxs.get(key)
         if ctx is None:
@@ -192,7 +199,7 @@ def _launch_args(t, stream, ctx):
     context of (device, stream)."""
     dev = t.device.index
     h = _stream_handle(dev, stream)
-    return (ctx if ctx is not None else context(dev, h)), ctypes.c_void_p(h)
+    return (ctx if ctx is not None else context(dev, h)), h
 
 
 def _u32_tensor(t, name):
@@ -217,8 +224,8 @@ def sort(keys, payload=None, variant=AUTO, stream=None, ctx=None, noalloc=False)
     lib = load_library()
     fn = lib.meld_sort_u32_noalloc if noalloc else lib.meld_sort_u32
     _check(fn(
-        c, ctypes.c_void_p(keys.data_ptr()),
-        None if payload is None else ctypes.c_void_p(payload.data_ptr()), keys.numel(),
+        c, keys.data_ptr(),
+        None if payload is None else payload.data_ptr(), keys.numel(),
         _variant(variant), s))
     return keys if payload is None else (keys, payload)
 
@@ -236,8 +243,8 @@ def sort_timed(keys, payload=None, variant=AUTO, stream=None, ctx=None) -> list[
     out = (ctypes.c_float * cap)()
     n_out = ctypes.c_size_t(0)
     _check(load_library().meld_sort_u32_timed(
-        c, ctypes.c_void_p(keys.data_ptr()),
-        None if payload is None else ctypes.c_void_p(payload.data_ptr()), keys.numel(),
+        c, keys.data_ptr(),
+        None if payload is None else payload.data_ptr(), keys.numel(),
         _variant(variant), s, out, cap, ctypes.byref(n_out)))
     return [float(out[i]) for i in range(n_out.value)]
 
@@ -249,8 +256,8 @@ def sort_steps(keys, payload=None, max_steps=-1, variant=AUTO, stream=None, ctx=
         _u32_tensor(payload, "payload")
     c, s = _launch_args(keys, stream, ctx)
     _check(load_library().meld_sort_u32_steps(
-        c, ctypes.c_void_p(keys.data_ptr()),
-        None if payload is None else ctypes.c_void_p(payload.data_ptr()), keys.numel(),
+        c, keys.data_ptr(),
+        None if payload is None else payload.data_ptr(), keys.numel(),
         int(max_steps), _variant(variant), s))
     return keys if payload is None else (keys, payload)
 
@@ -269,8 +276,8 @@ def segmented_sort(keys, offsets, variant=AUTO, stream=None, low=None, high=None
         return keys
     lib = load_library()
     c, s = _launch_args(keys, stream, ctx)
-    args = (c, ctypes.c_void_p(keys.data_ptr()), keys.numel(),
-            ctypes.c_void_p(offsets.data_ptr()), nseg)
+    args = (c, keys.data_ptr(), keys.numel(),
+            offsets.data_ptr(), nseg)
     if low is None and high is None:
         _check(lib.meld_segmented_sort_u32(*args, _variant(variant), s))
     else:
@@ -334,8 +341,8 @@ def divergent_region(x, tab, seed: int, thr: int, side_true, side_false, variant
     lib = load_library()
     fn = lib.meld_probe_region_gathers if gathers_only else lib.meld_divergent_region_f32
     _check(fn(
-        c, ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(out.data_ptr()), x.numel(),
-        ctypes.c_void_p(tab.data_ptr()), tab.numel(), int(seed), int(thr),
+        c, x.data_ptr(), out.data_ptr(), x.numel(),
+        tab.data_ptr(), tab.numel(), int(seed), int(thr),
         _as_side(side_true), _as_side(side_false), _variant(variant), s))
     return out
 
@@ -347,7 +354,7 @@ def oddeven_sort_buckets(keys, log_bucket: int, max_steps: int = -1, variant=AUT
     _u32_tensor(keys, "keys")
     c, s = _launch_args(keys, stream, ctx)
     _check(load_library().meld_oddeven_sort_buckets_u32(
-        c, ctypes.c_void_p(keys.data_ptr()), keys.numel(), int(log_bucket), int(max_steps),
+        c, keys.data_ptr(), keys.numel(), int(log_bucket), int(max_steps),
         _variant(variant), s))
 
 
@@ -356,7 +363,7 @@ def merge_sort(keys, max_passes: int = -1, variant=AUTO, stream=None, ctx=None):
     _u32_tensor(keys, "keys")
     c, s = _launch_args(keys, stream, ctx)
     _check(load_library().meld_merge_sort_u32(
-        c, ctypes.c_void_p(keys.data_ptr()), keys.numel(), int(max_passes), _variant(variant),
+        c, keys.data_ptr(), keys.numel(), int(max_passes), _variant(variant),
         s))
 
 
@@ -366,8 +373,8 @@ def region3(x, tab, seed: int, thr0: int, thr1: int, way0, way1, way2, variant=A
     out = _region_tensors(x, tab, out)
     c, s = _launch_args(x, stream, ctx)
     _check(load_library().meld_region3_f32(
-        c, ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(out.data_ptr()), x.numel(),
-        ctypes.c_void_p(tab.data_ptr()), tab.numel(), int(seed), int(thr0), int(thr1),
+        c, x.data_ptr(), out.data_ptr(), x.numel(),
+        tab.data_ptr(), tab.numel(), int(seed), int(thr0), int(thr1),
         _as_side(way0), _as_side(way1), _as_side(way2), _variant(variant), s))
     return out
 
@@ -386,8 +393,8 @@ def region_lanetrips(x, tab, seed: int, thr: int, side_true, side_false, variant
     out = _region_tensors(x, tab, out)
     c, s = _launch_args(x, stream, ctx)
     _check(load_library().meld_region_lanetrips_f32(
-        c, ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(out.data_ptr()), x.numel(),
-        ctypes.c_void_p(tab.data_ptr()), tab.numel(), int(seed), int(thr),
+        c, x.data_ptr(), out.data_ptr(), x.numel(),
+        tab.data_ptr(), tab.numel(), int(seed), int(thr),
         _as_side_range(side_true), _as_side_range(side_false), _variant(variant), s))
     return out
 
@@ -418,7 +425,7 @@ def probe_segments(offsets, stream=None, ctx=None):
     _u32_tensor(offsets, "offsets")
     out = (ctypes.c_uint64 * 4)()
     c, s = _launch_args(offsets, stream, ctx)
-    _check(load_library().meld_probe_segments(c, ctypes.c_void_p(offsets.data_ptr()),
+    _check(load_library().meld_probe_segments(c, offsets.data_ptr(),
                                               max(offsets.numel() - 1, 0), out, s))
     return (int(out[0]), int(out[1])), (int(out[2]), int(out[3]))
 
