@@ -109,8 +109,8 @@ def _dist(np, samples_ms, scale=1e3):
 
 def _tuned_region_form(meld, tt, tf):
     """The form MELD_AUTO chose for the 2^24-lane region at p = 0.5 with trips (tt, tf)."""
-    names = {0: "divergent", 1: "melded", 2: "melded_inplace"}
-    key = f"n=24 tab=24 tT={tt} tF={tf} p10=5"
+    names = {0: "divergent", 1: "melded", 3: "melded_inplace", 4: "four_lanes"}
+    key = f"n=24 tab=24 tT={tt} tF={tf} p10=5 q"
     for e in json.loads(meld.plan_describe())["entries"]:
         if e["op"] == "region" and e["key"] == key:
             return names.get(e["form"], str(e["form"]))

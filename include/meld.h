@@ -361,7 +361,7 @@ meld_status meld_probe_region_gathers(meld_ctx *ctx, const float *x, float *y, s
  * next ones across the two longest, the rest by the longest way alone
  * (multiplier selected per lane, each way's gathers in one conditional
  * block); MELD_MELDED_INPLACE aligns the gathers as well. MELD_AUTO times the
- * three forms once per shape class.
+ * three forms, and one with four lanes per thread, once per shape class.
  *
  * Arguments as for meld_divergent_region_f32; thr0 <= thr1 <= 2^32.
  * Errors:  as meld_divergent_region_f32, plus MELD_EINVAL for thr0 > thr1.
@@ -386,8 +386,8 @@ typedef struct {
  *                 mod (s.trips_hi - s.trips_lo + 1))
  * steps, otherwise as meld_divergent_region_f32. The melded form runs one
  * loop for both sides, each lane leaving after its own count; the divergent
- * one runs each side's loop in turn. MELD_AUTO times the three forms once per
- * shape class.
+ * one runs each side's loop in turn. MELD_AUTO times the three forms, and one
+ * with four lanes per thread, once per shape class.
  *
  * Arguments as for meld_divergent_region_f32; trips_lo <= trips_hi <= 65536.
  * Errors:  as meld_divergent_region_f32, plus MELD_EINVAL for a range with
@@ -432,9 +432,10 @@ meld_status meld_probe_segments(meld_ctx *ctx, const uint32_t *offsets, size_t n
  * trip counts and p in tenths). The first call of a class times the
  * candidates on the caller's stream — sorts on a scratch copy of the input
  * (tile size x divergent/melded per stage), the region on the caller's own
- * arrays (its three forms) — runs the matching divergence probe, and keeps
- * the decision (see meld_tune_choose). Later calls reuse it. A stream that is
- * being captured gets the untuned default (melded) without timing. */
+ * arrays (its three forms, and one with four lanes per thread) — runs the matching divergence probe, and keeps
+ * the decision (see meld_tune_choose). Later calls reuse it. An entry's key also
+ * names the candidates ("r", "q"), so that a file of a library with fewer of them
+ * is read but its entries are timed anew. A stream that is being captured gets the untuned default (melded) without timing. */
 
 /* Loads decisions from the JSON file cache_path (if it exists and was
  * written on the same GPU architecture and HIP runtime) and saves every new

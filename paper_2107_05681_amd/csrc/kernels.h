@@ -13,7 +13,9 @@ struct RegionSide {
     uint32_t trips;
 };
 
-enum class RegionForm { kDivergent, kMelded, kMeldedInPlace };
+// kQuad: four lanes per thread (region_quad.hip); launch_region and its variants
+// take the other three.
+enum class RegionForm { kDivergent, kMelded, kMeldedInPlace, kQuad };
 
 hipError_t launch_region(const float *x, float *y, uint32_t n, const float *tab, uint32_t mask,
                          uint64_t seed, uint64_t thr, RegionSide T, RegionSide F, RegionForm form,
@@ -44,6 +46,17 @@ struct RegionSideRange {
 hipError_t launch_region_lanetrips(const float *x, float *y, uint32_t n, const float *tab,
                                    uint32_t mask, uint64_t seed, uint64_t thr, RegionSideRange T,
                                    RegionSideRange F, RegionForm form, hipStream_t stream);
+
+// The same regions with four consecutive lanes per thread (region_quad.hip).
+hipError_t launch_region_quad(const float *x, float *y, uint32_t n, const float *tab,
+                              uint32_t mask, uint64_t seed, uint64_t thr, RegionSide T,
+                              RegionSide F, hipStream_t stream);
+hipError_t launch_region3_quad(const float *x, float *y, uint32_t n, const float *tab,
+                               uint32_t mask, uint64_t seed, uint64_t thr0, uint64_t thr1,
+                               RegionSide W0, RegionSide W1, RegionSide W2, hipStream_t stream);
+hipError_t launch_region_lanetrips_quad(const float *x, float *y, uint32_t n, const float *tab,
+                                        uint32_t mask, uint64_t seed, uint64_t thr,
+                                        RegionSideRange T, RegionSideRange F, hipStream_t stream);
 
 // Array with virtual padding: position p < n lives in keys/vals[p]; positions
 // n <= p < N hold the sentinel, the largest value, and have no memory.

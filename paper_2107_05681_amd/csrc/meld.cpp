@@ -1022,58 +1022,63 @@ meld::RegionForm region_form(meld_variant v) {
                                       : meld::RegionForm::kMelded;
 }
 
-// MELD_AUTO for the region: the tuned form of this shape class, timing the
-// three forms on the caller's arrays (the final run overwrites y).
-meld_status auto_region_form(meld_ctx *ctx, const float *x, float *y, size_t n, const float *tab,
-                             size_t tab_len, uint64_t seed, uint64_t thr,
-                             const meld::RegionSide &T, const meld::RegionSide &F, hipStream_t s,
-                             meld::RegionForm *out) {
+// The region forms MELD_AUTO times, and their codes in the tuner's entries.
+constexpr meld::RegionForm kAutoForms[] = {meld::RegionForm::kDivergent, meld::RegionForm::kMelded,
+                                           meld::RegionForm::kMeldedInPlace,
+                                           meld::RegionForm::kQuad};
+constexpr int kAutoFormCodes[] = {0, 1, 3, 4};
+constexpr int kAutoFormCount = 4;
+
+// MELD_AUTO for the regions: the tuned form of this shape class, timing the
+// forms on the caller's arrays the first time (the final run overwrites y).
+// probe(&mixed) measures the share of mixed waves. The key is the caller's plus
+// a letter for the candidates, so that a decision made without the last form is
+// not taken for one made with it.
+template <typename Launch, typename Probe>
+meld_status auto_timed_form(meld_ctx *ctx, const char *op, const std::string &shape, Launch launch,
+                            Probe probe, hipStream_t s, meld::RegionForm *out) {
     *out = meld::RegionForm::kMelded;
-    const uint32_t p10 = (uint32_t)((thr * 10 + (1ull << 31)) >> 32);
-    const std::string key = fmt("n=%u tab=%u tT=%u tF=%u p10=%u", log2_ceil(n), log2_ceil(tab_len),
-                                T.trips, F.trips, p10);
-    if (const meld::TuneEntry *t = ctx->tuner.find("region", key)) {
-        *out = t->form == 0   ? meld::RegionForm::kDivergent
-               : t->form == 3 ? meld::RegionForm::kMeldedInPlace
-                              : meld::RegionForm::kMelded;
+    const std::string key = shape + " q";
+    if (const meld::TuneEntry *t = ctx->tuner.find(op, key)) {
+        for (int f = 0; f < kAutoFormCount; ++f)
+            if (kAutoFormCodes[f] == t->form) *out = kAutoForms[f];
         return MELD_OK;
     }
     if (capturing(s)) return MELD_OK;
-    const meld::RegionForm forms[3] = {meld::RegionForm::kDivergent, meld::RegionForm::kMelded,
-                                       meld::RegionForm::kMeldedInPlace};
-    const int codes[3] = {0, 1, 3};
-    double ms[3];
-    int flo[3], fhi[3];
-    for (int f = 0; f < 3; ++f) {
-        const meld::RegionForm form = forms[f];
+    double ms[kAutoFormCount];
+    int flo[kAutoFormCount];
+    for (int f = 0; f < kAutoFormCount; ++f) {
         auto run = [&]() -> meld_status {
-            hipError_t r = meld::launch_region(x, y, (uint32_t)n, tab, (uint32_t)(tab_len - 1),
-                                               seed, thr, T, F, form, s);
+            hipError_t r = launch(kAutoForms[f]);
             return r == hipSuccess ? MELD_OK : hip_fail(r, "region launch");
         };
         meld_status st = run();  // warm-up
         if (st != MELD_OK) return st;
         st = time_median(s, 3, []() { return MELD_OK; }, run, &ms[f]);
         if (st != MELD_OK) return st;
-        flo[f] = fhi[f] = f == 0 ? 0 : 1;
+        flo[f] = f == 0 ? 0 : 1;
     }
-    unsigned long long c[3] = {0};
-    meld_status st = run_probe(ctx, s, 3, c, [&](unsigned long long *o) {
-        return meld::launch_probe_region((uint32_t)n, seed, thr, o, s);
-    });
+    double mixed = 1.0;
+    meld_status st = probe(&mixed);
     if (st != MELD_OK) return st;
-    const double mixed = c[2] ? (double)c[0] / (double)c[2] : 0.0;
-    const int pick = meld::choose(3, ms, flo, fhi, mixed, mixed, ctx->theta, ctx->tie);
-    *out = forms[pick];
+    const int pick =
+        meld::choose(kAutoFormCount, ms, flo, flo, mixed, mixed, ctx->theta, ctx->tie);
+    *out = kAutoForms[pick];
     meld::TuneEntry te;
-    te.op = "region";
+    te.op = op;
     te.key = key;
     te.lo = te.hi = flo[pick];
-    te.form = codes[pick];
+    te.form = kAutoFormCodes[pick];
     te.ms = ms[pick];
     te.mixed_lo = te.mixed_hi = mixed;
-    te.trials = 3;
+    te.trials = kAutoFormCount;
     ctx->tuner.put(te);
+    return MELD_OK;
+}
+
+// The variants count every wave as mixed.
+meld_status all_mixed(double *mixed) {
+    *mixed = 1.0;
     return MELD_OK;
 }
 
@@ -1094,50 +1099,6 @@ meld_status check_region_pointers(const char *name, meld_ctx *ctx, const float *
         return fail(MELD_EINVAL, "%s: x, y and tab must be device pointers on device %d", name,
                     ctx->device);
     if (x == y) return fail(MELD_EINVAL, "%s: y aliases x", name);
-    return MELD_OK;
-}
-
-// MELD_AUTO for the region variants: times the three forms once per shape
-// class on the caller's arrays (the final run overwrites y) and keeps the
-// fastest, preferring the melded ones within the tie margin.
-template <typename Launch>
-meld_status auto_timed_form(meld_ctx *ctx, const char *op, const std::string &key, Launch launch,
-                            hipStream_t s, meld::RegionForm *out) {
-    *out = meld::RegionForm::kMelded;
-    if (const meld::TuneEntry *t = ctx->tuner.find(op, key)) {
-        *out = t->form == 0   ? meld::RegionForm::kDivergent
-               : t->form == 3 ? meld::RegionForm::kMeldedInPlace
-                              : meld::RegionForm::kMelded;
-        return MELD_OK;
-    }
-    if (capturing(s)) return MELD_OK;
-    const meld::RegionForm forms[3] = {meld::RegionForm::kDivergent, meld::RegionForm::kMelded,
-                                       meld::RegionForm::kMeldedInPlace};
-    const int codes[3] = {0, 1, 3};
-    double ms[3];
-    int flo[3], fhi[3];
-    for (int f = 0; f < 3; ++f) {
-        auto run = [&]() -> meld_status {
-            hipError_t r = launch(forms[f]);
-            return r == hipSuccess ? MELD_OK : hip_fail(r, "region launch");
-        };
-        meld_status st = run();  // warm-up
-        if (st != MELD_OK) return st;
-        st = time_median(s, 3, []() { return MELD_OK; }, run, &ms[f]);
-        if (st != MELD_OK) return st;
-        flo[f] = fhi[f] = f == 0 ? 0 : 1;
-    }
-    const int pick = meld::choose(3, ms, flo, fhi, 1.0, 1.0, ctx->theta, ctx->tie);
-    *out = forms[pick];
-    meld::TuneEntry te;
-    te.op = op;
-    te.key = key;
-    te.lo = te.hi = flo[pick];
-    te.form = codes[pick];
-    te.ms = ms[pick];
-    te.mixed_lo = te.mixed_hi = 1.0;
-    te.trials = 3;
-    ctx->tuner.put(te);
     return MELD_OK;
 }
 
@@ -1243,12 +1204,38 @@ meld_status region_entry(meld_ctx *ctx, const float *x, float *y, size_t n, cons
     const meld::RegionSide F{side_false.a, side_false.off, side_false.step, side_false.trips};
     const hipStream_t s = static_cast<hipStream_t>(stream);
     meld::RegionForm form = region_form(variant);
+    auto launch = [&](meld::RegionForm f) {
+        if (f == meld::RegionForm::kQuad)
+            return meld::launch_region_quad(x, y, (uint32_t)n, tab, (uint32_t)(tab_len - 1), seed,
+                                            thr, T, F, s);
+        return meld::launch_region(x, y, (uint32_t)n, tab, (uint32_t)(tab_len - 1), seed, thr, T, F,
+                                   f, s);
+    };
     if (variant == MELD_AUTO) {
-        meld_status st = auto_region_form(ctx, x, y, n, tab, tab_len, seed, thr, T, F, s, &form);
+        const uint32_t p10 = (uint32_t)((thr * 10 + (1ull << 31)) >> 32);
+        auto probe = [&](double *mixed) -> meld_status {
+            unsigned long long c[3] = {0};
+            meld_status st = run_probe(ctx, s, 3, c, [&](unsigned long long *o) {
+                return meld::launch_probe_region((uint32_t)n, seed, thr, o, s);
+            });
+            *mixed = c[2] ? (double)c[0] / (double)c[2] : 0.0;
+            return st;
+        };
+        meld_status st = auto_timed_form(ctx, "region",
+                                         fmt("n=%u tab=%u tT=%u tF=%u p10=%u", log2_ceil(n),
+                                             log2_ceil(tab_len), T.trips, F.trips, p10),
+                                         launch, probe, s, &form);
         if (st != MELD_OK) return st;
     }
-    auto launch = gathers_only ? meld::launch_region_gathers : meld::launch_region;
-    hipError_t e = launch(x, y, (uint32_t)n, tab, (uint32_t)(tab_len - 1), seed, thr, T, F, form, s);
+    hipError_t e = hipSuccess;
+    if (gathers_only) {
+        // The four-lane form has no such probe: the melded one stands in.
+        if (form == meld::RegionForm::kQuad) form = meld::RegionForm::kMelded;
+        e = meld::launch_region_gathers(x, y, (uint32_t)n, tab, (uint32_t)(tab_len - 1), seed, thr,
+                                        T, F, form, s);
+    } else {
+        e = launch(form);
+    }
     if (e != hipSuccess) return hip_fail(e, "region launch");
     return MELD_OK;
 }
@@ -1590,6 +1577,9 @@ meld_status meld_region3_f32(meld_ctx *ctx, const float *x, float *y, size_t n,
     const meld::RegionSide W2{way2.a, way2.off, way2.step, way2.trips};
     const hipStream_t s = static_cast<hipStream_t>(stream);
     auto launch = [&](meld::RegionForm f) {
+        if (f == meld::RegionForm::kQuad)
+            return meld::launch_region3_quad(x, y, (uint32_t)n, tab, (uint32_t)(tab_len - 1), seed,
+                                             thr0, thr1, W0, W1, W2, s);
         return meld::launch_region3(x, y, (uint32_t)n, tab, (uint32_t)(tab_len - 1), seed, thr0,
                                     thr1, W0, W1, W2, f, s);
     };
@@ -1600,7 +1590,7 @@ meld_status meld_region3_f32(meld_ctx *ctx, const float *x, float *y, size_t n,
         const std::string key =
             fmt("n=%u tab=%u t=%u,%u,%u p10=%u,%u", log2_ceil(n), log2_ceil(tab_len), W0.trips,
                 W1.trips, W2.trips, p0, p1);
-        st = auto_timed_form(ctx, "region3", key, launch, s, &form);
+        st = auto_timed_form(ctx, "region3", key, launch, all_mixed, s, &form);
         if (st != MELD_OK) return st;
     }
     hipError_t e = launch(form);
@@ -1632,6 +1622,9 @@ meld_status meld_region_lanetrips_f32(meld_ctx *ctx, const float *x, float *y, s
                                   side_false.trips_lo, side_false.trips_hi - side_false.trips_lo};
     const hipStream_t s = static_cast<hipStream_t>(stream);
     auto launch = [&](meld::RegionForm f) {
+        if (f == meld::RegionForm::kQuad)
+            return meld::launch_region_lanetrips_quad(x, y, (uint32_t)n, tab,
+                                                      (uint32_t)(tab_len - 1), seed, thr, T, F, s);
         return meld::launch_region_lanetrips(x, y, (uint32_t)n, tab, (uint32_t)(tab_len - 1), seed,
                                              thr, T, F, f, s);
     };
@@ -1642,7 +1635,7 @@ meld_status meld_region_lanetrips_f32(meld_ctx *ctx, const float *x, float *y, s
             fmt("n=%u tab=%u T=%u-%u F=%u-%u p10=%u", log2_ceil(n), log2_ceil(tab_len),
                 side_true.trips_lo, side_true.trips_hi, side_false.trips_lo, side_false.trips_hi,
                 p10);
-        st = auto_timed_form(ctx, "region_lanetrips", key, launch, s, &form);
+        st = auto_timed_form(ctx, "region_lanetrips", key, launch, all_mixed, s, &form);
         if (st != MELD_OK) return st;
     }
     hipError_t e = launch(form);
