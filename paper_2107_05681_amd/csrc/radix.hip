@@ -34,7 +34,7 @@ struct RadixArgs {
     uint32_t pass;     // 0 .. 3
     uint32_t tiles;    // tiles that cover n
     uint32_t stride;   // row length of counts: tiles, rounded up to 16
-    uint32_t *counts;  // [digit][tile]
+    uint32_t *counts;  // [digit][tile]; unscanned [tile][digit], 16 bits each
     uint32_t *totals;  // [digit]
     uint32_t *part;    // [count workgroup]: differing bits, then disorder
     uint32_t parts;    // count workgroups
@@ -106,7 +106,7 @@ __device__ __forceinline__ uint32_t wave_exclusive_scan(uint32_t x, uint32_t lan
 // tiles go to the XCDs in contiguous ranges, so that the short pieces of the
 // count rows that neighbours write meet in one L2. FIRST (pass 0): also the bits that
 // differ from the array's first value and whether a value exceeds the next.
-template <int TILE, int TPB, bool NTL, bool FIRST>
+template <int TILE, int TPB, bool NTL, bool FIRST, bool SCANNED>
 __global__ __launch_bounds__(256 * TPB) void radix_count_kernel(RadixArgs a) {
     constexpr int Q = TILE / (256 * 4);  // 16-byte loads per lane
     __shared__ uint32_t hist[TPB][kDigits];
@@ -175,7 +175,11 @@ __global__ __launch_bounds__(256 * TPB) void radix_count_kernel(RadixArgs a) {
         }
     }
     __syncthreads();
-    if (t < kDigits) {
+    if constexpr (!SCANNED) {
+        static_assert(TPB == 1 && TILE <= 0xFFFF, "16-bit counts of one tile");
+        if (t < kDigits / 2)
+            a.counts[(size_t)tile * (kDigits / 2) + t] = h[2 * t] | (h[2 * t + 1] << 16);
+    } else if (t < kDigits) {
         uint32_t *row = a.counts + (size_t)t * a.stride + group * TPB;
         if constexpr (TPB == 4) {
             *reinterpret_cast<uint4 *>(row) =
@@ -294,6 +298,65 @@ constexpr size_t radix_lds_bytes() {
     return (size_t)NT * ITEMS * 4 + (NT / 64) * kDigits * 2 + kDigits * 4;
 }
 
+// Sums of the digits' counts over all tiles, to s[0 .. 256), and over the tiles
+// before tile_id, to s[NT / 64 * 256 ..): half a wave reads a tile's 512 bytes, 16
+// per lane (eight digits), every half wave tiles of its own, eight of them at a
+// time. A launch for the scan costs as much at 256 tiles (2^17 keys, 64 tiles: 41 us
+// a sort with the scan, 37 so; 2^18 pairs with their index, 128 tiles: 68 and 61;
+// 2^19 keys, 256 tiles: 46 and 52).
+template <int NT>
+__device__ __forceinline__ void radix_add_counts(const RadixArgs &a, uint32_t tile_id,
+                                                 uint32_t *s) {
+    constexpr uint32_t W = NT / 64, G = NT / 32;
+    constexpr int U = 8;  // rows in flight
+    const uint32_t t = threadIdx.x, l = t & 31, w = t / 64;
+    const uint4 *rows = reinterpret_cast<const uint4 *>(a.counts) + l;
+    uint32_t tot[8] = {}, own[8] = {};
+    for (uint32_t b0 = t / 32; b0 < a.tiles; b0 += U * G) {
+        uint4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t b = b0 + u * G;
+            v[u] = make_uint4(0, 0, 0, 0);
+            if (b < a.tiles) v[u] = rows[b * 32];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t before = b0 + u * G < tile_id ? ~0u : 0u;
+            const uint32_t x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                tot[2 * q] += x[q] & 0xFFFF;
+                tot[2 * q + 1] += x[q] >> 16;
+                const uint32_t y = x[q] & before;
+                own[2 * q] += y & 0xFFFF;
+                own[2 * q + 1] += y >> 16;
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        tot[q] += (uint32_t)__shfl_xor((int)tot[q], 32);
+        own[q] += (uint32_t)__shfl_xor((int)own[q], 32);
+    }
+    // The wave's lower half stores the totals, the upper one the prefixes.
+    const bool upper = (t & 32) != 0;
+    uint4 *to = reinterpret_cast<uint4 *>(s + (upper ? W * kDigits : 0) + w * kDigits + 8 * l);
+    to[0] = upper ? make_uint4(own[0], own[1], own[2], own[3])
+                  : make_uint4(tot[0], tot[1], tot[2], tot[3]);
+    to[1] = upper ? make_uint4(own[4], own[5], own[6], own[7])
+                  : make_uint4(tot[4], tot[5], tot[6], tot[7]);
+    __syncthreads();
+    for (uint32_t i = t; i < 2 * kDigits; i += NT) {
+        uint32_t *c = s + (i < kDigits ? i : W * kDigits + i - kDigits);
+        uint32_t sum = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < W; ++q) sum += c[q * kDigits];
+        c[0] = sum;
+    }
+    __syncthreads();
+}
+
 // One tile of NT * ITEMS elements per workgroup: ranks within each wave by
 // ballots (the lanes with an equal digit), prefixes over waves and digits, the
 // tile brought into digit order in LDS, runs of equal digits written out. Pairs
@@ -311,7 +374,7 @@ constexpr size_t radix_lds_bytes() {
 // elements a tile: the counts per tile stay few and the tile's output and its
 // neighbours' stay in the L2. SCANNED: the counts hold
 // their prefix over the tiles; otherwise (few tiles) every workgroup adds
-// them up itself, and in pass 0 decides which passes run.
+// them up itself (radix_add_counts), and in pass 0 decides which passes run.
 template <bool PAIRS, int NT, int ITEMS, bool NTL, bool SCANNED>
 __global__ __launch_bounds__(NT) void radix_scatter_kernel(RadixArgs a) {
     constexpr uint32_t W = NT / 64;
@@ -325,9 +388,12 @@ __global__ __launch_bounds__(NT) void radix_scatter_kernel(RadixArgs a) {
 
     uint32_t run;
     if (!SCANNED && a.pass == 0) {
-        const bool in = lane < a.parts;
-        run = passes_to_run(wave_or(in ? a.part[lane] : 0),
-                            wave_or(in ? a.part[a.parts + lane] : 0) == 0);
+        uint32_t diff = 0, bad = 0;
+        for (uint32_t b = lane; b < a.parts; b += 64) {
+            diff |= a.part[b];
+            bad |= a.part[a.parts + b];
+        }
+        run = passes_to_run(wave_or(diff), wave_or(bad) == 0);
         if (blockIdx.x == 0 && t == 0) *a.ctl = run;
     } else {
         run = *a.ctl;
@@ -369,26 +435,10 @@ __global__ __launch_bounds__(NT) void radix_scatter_kernel(RadixArgs a) {
                 pre[3] += at + tot.x + tot.y + tot.z;
             }
         } else {
-            for (uint32_t d = t; d < kDigits; d += NT) {
-                const uint4 *row = reinterpret_cast<const uint4 *>(a.counts + d * a.stride);
-                uint32_t tot = 0, own = 0;
-#pragma unroll 4
-                for (uint32_t b = 0; b < a.tiles; b += 4) {
-                    const uint4 c = row[b / 4];
-                    const uint32_t cc[4] = {c.x, c.y, c.z, c.w};
-#pragma unroll
-                    for (uint32_t q = 0; q < 4; ++q) {
-                        if (b + q < a.tiles) tot += cc[q];
-                        if (b + q < tile_id) own += cc[q];
-                    }
-                }
-                exch[d] = tot;
-                exch[kDigits + d] = own;
-            }
-            __syncthreads();
+            radix_add_counts<NT>(a, tile_id, exch);
             if (w == 0) {
                 const uint4 tot = reinterpret_cast<const uint4 *>(exch)[lane];
-                const uint4 own = reinterpret_cast<const uint4 *>(exch + kDigits)[lane];
+                const uint4 own = reinterpret_cast<const uint4 *>(exch + W * kDigits)[lane];
                 const uint32_t at = wave_exclusive_scan(tot.x + tot.y + tot.z + tot.w, lane);
                 pre[0] = at + own.x;
                 pre[1] = at + tot.x + own.y;
@@ -516,7 +566,8 @@ __global__ __launch_bounds__(NT) void radix_scatter_kernel(RadixArgs a) {
 enum class RadixTile { kSmall, kMid, kLarge };
 constexpr uint32_t kSmallTile = 2048, kMidTile = 4096, kLargeTile = 8192;
 constexpr uint32_t kSmallMax = 1u << 19, kMidMax = 12u << 20;
-constexpr uint32_t kUnscannedTiles = 64;  // kSmall: up to so many tiles need no scan
+constexpr uint32_t kUnscannedTiles = 128;  // kSmall: up to so many tiles need no scan
+static_assert(kUnscannedTiles * kSmallTile <= kSmallMax, "other tiles are always scanned");
 
 struct RadixShape {
     RadixTile kind;
@@ -545,13 +596,13 @@ size_t radix_table_words(const RadixShape &r) {
            padded_words(2 * (size_t)r.parts) + padded_words(1);
 }
 
-template <int TILE, int TPB, bool NTL>
+template <int TILE, int TPB, bool NTL, bool SCANNED>
 void count(const RadixArgs &a, hipStream_t s) {
     if (a.pass == 0)
-        hipLaunchKernelGGL((radix_count_kernel<TILE, TPB, NTL, true>), dim3(a.parts),
+        hipLaunchKernelGGL((radix_count_kernel<TILE, TPB, NTL, true, SCANNED>), dim3(a.parts),
                            dim3(256 * TPB), 0, s, a);
     else
-        hipLaunchKernelGGL((radix_count_kernel<TILE, TPB, NTL, false>), dim3(a.parts),
+        hipLaunchKernelGGL((radix_count_kernel<TILE, TPB, NTL, false, SCANNED>), dim3(a.parts),
                            dim3(256 * TPB), 0, s, a);
 }
 
@@ -565,24 +616,22 @@ void scatter(const RadixArgs &a, hipStream_t s) {
 
 template <bool PAIRS>
 hipError_t radix_pass(const RadixShape &r, const RadixArgs &a, hipStream_t s) {
-    switch (r.kind) {
-        case RadixTile::kSmall: count<kSmallTile, 1, false>(a, s); break;
-        case RadixTile::kMid: count<kMidTile, 1, false>(a, s); break;
-        default: count<kLargeTile, 4, true>(a, s); break;
-    }
-    if (r.scanned) {
-        if (r.tiles <= 1024)
-            hipLaunchKernelGGL(radix_scan_kernel<64>, dim3(kDigits), dim3(64), 0, s, a);
-        else
-            hipLaunchKernelGGL(radix_scan_kernel<1024>, dim3(kDigits), dim3(1024), 0, s, a);
+    if (!r.scanned) {
+        count<kSmallTile, 1, false, false>(a, s);
+        scatter<PAIRS, 256, 8, false, false>(a, s);
+        return hipGetLastError();
     }
     switch (r.kind) {
-        case RadixTile::kSmall:
-            if (r.scanned)
-                scatter<PAIRS, 256, 8, false, true>(a, s);
-            else
-                scatter<PAIRS, 256, 8, false, false>(a, s);
-            break;
+        case RadixTile::kSmall: count<kSmallTile, 1, false, true>(a, s); break;
+        case RadixTile::kMid: count<kMidTile, 1, false, true>(a, s); break;
+        default: count<kLargeTile, 4, true, true>(a, s); break;
+    }
+    if (r.tiles <= 1024)
+        hipLaunchKernelGGL(radix_scan_kernel<64>, dim3(kDigits), dim3(64), 0, s, a);
+    else
+        hipLaunchKernelGGL(radix_scan_kernel<1024>, dim3(kDigits), dim3(1024), 0, s, a);
+    switch (r.kind) {
+        case RadixTile::kSmall: scatter<PAIRS, 256, 8, false, true>(a, s); break;
         case RadixTile::kMid: scatter<PAIRS, 512, 8, false, true>(a, s); break;
         default:
             if constexpr (PAIRS)
