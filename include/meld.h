@@ -131,13 +131,15 @@ const char *meld_last_error(void);
  * the padding (0xFFFFFFFF, for pairs (0xFFFFFFFF, 0xFFFFFFFF)) never leaves
  * the positions n..N-1, takes no memory and no work, and nothing past n is
  * read or written in the caller's arrays.
- * MELD_AUTO runs the network up to 2^15 keys or 2^17 pairs, with
- * MELD_OPT_SORT_LOG_TILE or MELD_OPT_LANE_EXCHANGE set, under capture, and
- * where the scratch below cannot be allocated, except that without those
- * options one workgroup sorts 2^11 + 1 .. 2^14 keys in registers; otherwise a
- * least-significant-digit radix sort, which gives the same (unique) result in at most four
- * passes per word. Its scratch, owned by the context, is as large as the
- * arrays plus at most 1/8 of that for digit counts.
+ * MELD_AUTO runs the network up to 2^11 keys or 2^17 pairs, with
+ * MELD_OPT_SORT_LOG_TILE or MELD_OPT_LANE_EXCHANGE set, and above 2^14 keys or
+ * 2^17 pairs under capture or where the scratch below cannot be allocated.
+ * Otherwise it takes another sort, which gives the same (unique) result: one
+ * workgroup in registers up to 2^13 keys (2^14 without scratch), sorted runs
+ * and ranks up to 2^17 keys, and above a least-significant-digit radix sort in
+ * at most four passes per word. The scratch, owned by the context, is as large
+ * as the arrays plus at most 1/8 of that for digit counts (2^17 words for the
+ * ranks).
  *
  * keys:    device u32[n], sorted in place (unsigned order).
  * payload: NULL, or device u32[n] moved with its key. With a payload the
@@ -193,7 +195,7 @@ meld_status meld_sort_u32_steps(meld_ctx *ctx, uint32_t *keys, uint32_t *payload
  * into on-chip and HBM passes), as JSON in buf (NUL-terminated), without
  * launching anything; "sorts_by" says whether meld_sort_u32 on this context
  * runs this network or, under MELD_AUTO, another sort ("network", "registers",
- * "radix"):
+ * "ranks", "radix"):
  *   {"n", "log_n", "pairs", "tuned", "sorts_by", "log_tile", "low", "high",
  *    "hbm_passes", "steps", "passes": [{"kind", "steps", "m", "b_hi", "b_lo"}]}
  * kind "tile" (everything in one tile), "local" (every tile's phases up to
@@ -271,9 +273,9 @@ meld_status meld_oddeven_sort_buckets_u32(meld_ctx *ctx, uint32_t *keys, size_t 
  * sides (emit, advance, load the next key of that run) as written, the melded
  * form selects the emitted key and issues one load from a selected address.
  * Ties take run A first. MELD_AUTO with all passes sorts as meld_sort_u32 does
- * (up to 2^14 keys in registers, above by radix passes); with max_passes, under
- * capture of more than 2^14 keys, and without the memory for the radix scratch
- * it times both forms once per shape class.
+ * (in registers, by ranks or by radix passes); with max_passes, and above 2^14
+ * keys under capture or without the memory for the scratch, it times both forms
+ * once per shape class.
  *
  * keys:    device u32[n], n < 2^31.
  * Scratch: a second buffer of n keys (MELD_AUTO: at most 9/8 n), owned by the

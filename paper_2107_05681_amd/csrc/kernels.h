@@ -150,6 +150,11 @@ hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t n, uint32_
 hipError_t launch_bucket_sort(uint32_t *keys, uint32_t n, uint32_t log_bucket,
                               hipStream_t stream);
 
+// Sorts keys[0..n), n <= kRankSortMax, by runs and ranks (rank_sort.hip).
+// scratch: kRankSortMax u32, 16-byte aligned.
+constexpr uint32_t kRankSortMax = 1u << 17;
+hipError_t launch_rank_sort(uint32_t *keys, uint32_t n, uint32_t *scratch, hipStream_t stream);
+
 hipError_t launch_fill_u32(uint32_t *p, uint32_t value, size_t count, hipStream_t stream);
 
 // Seeded inputs generated on the device (gen.hip).

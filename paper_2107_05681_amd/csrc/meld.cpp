@@ -694,21 +694,7 @@ SortPlan fixed_plan(const meld_ctx *ctx, bool pairs, size_t n, meld_variant v) {
     return SortPlan{plan_log_tile(ctx, pairs, log2_ceil(n)), m, m, plan_xch(ctx)};
 }
 
-// Whether MELD_AUTO sorts n elements by the radix passes (radix.hip) rather
-// than by the network: above the sizes where their launches cost as much as
-// the network's (one MI355X, radix against the tuned network, microseconds:
-// keys 2^15 35 / 33, 49153 38 / 48, 2^16 38 / 42; pairs with their index
-// 49153 55 / 75, 2^17 63 / 74; pairs with random payloads, twice the passes,
-// 2^17 86 / 74, 196609 89 / 117). An option that fixes how the network runs
-// asks for the network. Not under capture: the recorded launches would hold
-// the address of scratch that a later call of the context may replace, where
-// the network of a power of two has none.
-bool radix_sorts(const meld_ctx *ctx, bool pairs, size_t n) {
-    return ctx->sort_log_tile == 0 && ctx->lane_exchange < 0 &&
-           n > (pairs ? (size_t)1 << 17 : (size_t)1 << 15);
-}
-
-// Sorts of up to so many keys take one workgroup (bucket_sort.hip).
+// Sorts of up to so many keys take one workgroup where they may (bucket_sort.hip).
 constexpr size_t kOneBucket = (size_t)1 << 14;
 
 meld_status sort_one_bucket(uint32_t *keys, size_t n, hipStream_t s) {
@@ -717,25 +703,43 @@ meld_status sort_one_bucket(uint32_t *keys, size_t n, hipStream_t s) {
     return e == hipSuccess ? MELD_OK : hip_fail(e, "bucket sort launch");
 }
 
-// Whether MELD_AUTO sorts n keys in one workgroup: above one wave's 2^11 keys,
-// where the network's tiles need several launches or many barriers (with the
-// copy of the input, bucket against the tuned network, microseconds: 2^11 10.9 /
-// 10.8, 3000 13.0 / 15.0, 2^12 12.0 / 14.8, 2^13 14.3 / 21.2, 2^14 23.9 / 29.3).
-bool bucket_sorts(const meld_ctx *ctx, bool pairs, size_t n) {
-    return !pairs && ctx->sort_log_tile == 0 && ctx->lane_exchange < 0 && n > ((size_t)1 << 11) &&
-           n <= kOneBucket;
+// How MELD_AUTO sorts n keys (with payloads) as far as the size decides:
+// kRegisters: one workgroup, above one wave's 2^11 keys, where the network's tiles
+//   need several launches or many barriers;
+// kRanks: runs and ranks (rank_sort.hip), which spread the work over the chip,
+//   until the searches, n times the number of runs, take longer than radix passes;
+// kRadix: radix passes (radix.hip), above the sizes where their launches cost as
+//   much as the network's.
+// One MI355X, with the copy of the input, microseconds, network / registers /
+// ranks / radix: 2^11 keys 10.8 / 10.9, 2^12 14.8 / 12.0, 2^13 21.2 / 14.3, 2^14
+// 29.3 / 23.9 / 19.5, 2^15 33 / - / 21.8 / 35, 2^16 42 / - / 25.6 / 36, 2^17 - / - / 33.6 /
+// 37; pairs with their index 49153 75 / - / - / 55, 2^17 74 / - / - / 63; pairs with
+// random payloads, twice the passes, 2^17 74 / - / - / 86, 196609 117 / - / - / 89. An
+// option that fixes how the network runs asks for the network. Ranks and radix passes not under capture: the
+// recorded launches would hold the address of scratch that a later call of the
+// context may replace, where the others have none.
+enum class SortBy { kNetwork, kRegisters, kRanks, kRadix };
+SortBy auto_sort_by(const meld_ctx *ctx, bool pairs, size_t n, bool scratch) {
+    if (ctx->sort_log_tile != 0 || ctx->lane_exchange >= 0) return SortBy::kNetwork;
+    if (pairs) return scratch && n > ((size_t)1 << 17) ? SortBy::kRadix : SortBy::kNetwork;
+    if (n <= ((size_t)1 << 11)) return SortBy::kNetwork;
+    if (scratch && n > ((size_t)1 << 13))
+        return n <= meld::kRankSortMax ? SortBy::kRanks : SortBy::kRadix;
+    return n <= kOneBucket ? SortBy::kRegisters : SortBy::kNetwork;
 }
 
-// The radix sort on the context's scratch; *done is false where that cannot be
-// allocated.
-meld_status try_radix_sort(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size_t n,
-                           hipStream_t s, bool *done) {
-    *done = ensure_words(&ctx->merge_buf, &ctx->merge_words,
-                         meld::radix_scratch_words((uint32_t)n, payload != nullptr),
-                         "radix scratch") == MELD_OK;
+// A sort by ranks or radix passes on the context's scratch; *done is false where
+// that cannot be allocated.
+meld_status try_scratch_sort(meld_ctx *ctx, SortBy by, uint32_t *keys, uint32_t *payload, size_t n,
+                             hipStream_t s, bool *done) {
+    const bool ranks = by == SortBy::kRanks;
+    const size_t words = ranks ? (size_t)meld::kRankSortMax
+                               : meld::radix_scratch_words((uint32_t)n, payload != nullptr);
+    *done = ensure_words(&ctx->merge_buf, &ctx->merge_words, words, "sort scratch") == MELD_OK;
     if (!*done) return MELD_OK;
-    hipError_t e = meld::launch_radix_sort(keys, payload, (uint32_t)n, ctx->merge_buf, s);
-    return e == hipSuccess ? MELD_OK : hip_fail(e, "radix sort launch");
+    hipError_t e = ranks ? meld::launch_rank_sort(keys, (uint32_t)n, ctx->merge_buf, s)
+                         : meld::launch_radix_sort(keys, payload, (uint32_t)n, ctx->merge_buf, s);
+    return e == hipSuccess ? MELD_OK : hip_fail(e, ranks ? "rank sort launch" : "radix sort launch");
 }
 
 // Probe of one tile's network: mixed-wave fraction of the phases k <= 64 and
@@ -1307,13 +1311,16 @@ meld_status meld_sort_u32(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size
         return fail(MELD_EINVAL, "meld_sort_u32: payload is not a device pointer on device %d",
                     ctx->device);
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    if (variant == MELD_AUTO && bucket_sorts(ctx, payload != nullptr, n))
-        return sort_one_bucket(keys, n, s);
-    if (variant == MELD_AUTO && radix_sorts(ctx, payload != nullptr, n) && !capturing(s)) {
-        // Without the memory for its scratch, the network, which needs none.
-        bool done = false;
-        meld_status st = try_radix_sort(ctx, keys, payload, n, s, &done);
-        if (done) return st;
+    if (variant == MELD_AUTO) {
+        const bool pairs = payload != nullptr;
+        SortBy by = auto_sort_by(ctx, pairs, n, !capturing(s));
+        if (by == SortBy::kRanks || by == SortBy::kRadix) {
+            bool done = false;
+            meld_status st = try_scratch_sort(ctx, by, keys, payload, n, s, &done);
+            if (done) return st;
+            by = auto_sort_by(ctx, pairs, n, false);
+        }
+        if (by == SortBy::kRegisters) return sort_one_bucket(keys, n, s);
     }
     SortPlan plan = fixed_plan(ctx, payload != nullptr, n, variant);
     if (variant == MELD_AUTO) {
@@ -1415,8 +1422,10 @@ meld_status meld_sort_plan_describe(meld_ctx *ctx, size_t n, int with_payload,
     bool tuned = false;
     const char *by = "network";
     if (ctx != nullptr) {
-        if (variant == MELD_AUTO && bucket_sorts(ctx, pairs, n)) by = "registers";
-        if (variant == MELD_AUTO && radix_sorts(ctx, pairs, n)) by = "radix";
+        if (variant == MELD_AUTO) {
+            constexpr const char *kNames[] = {"network", "registers", "ranks", "radix"};
+            by = kNames[(int)auto_sort_by(ctx, pairs, n, true)];
+        }
         plan.log_t = plan_log_tile(ctx, pairs, log_n);
         plan.xch = plan_xch(ctx);
         if (variant == MELD_AUTO) tuned = cached_sort_plan(ctx, pairs, log_n, &plan);
@@ -1506,15 +1515,17 @@ meld_status meld_merge_sort_u32(meld_ctx *ctx, uint32_t *keys, size_t n, int64_t
     const hipStream_t s = static_cast<hipStream_t>(stream);
     // All passes: only the sorted array counts (with the copy of the input, against
     // the faster form of the merge sort, microseconds: 1000 keys 10.3 / 17.6, 2^14
-    // 23.9 / 47.5, 2^15 35.6 / 62, 2^20 55 / 135, 2^24 228 / 696). Under capture, and
-    // without the memory for the radix scratch, the merge passes.
+    // 19.5 / 47.5, 2^15 21.8 / 62, 2^20 55 / 135, 2^24 228 / 696). Above 2^14 keys under
+    // capture, and without the memory for the scratch, the merge passes.
     if (variant == MELD_AUTO && max_passes < 0) {
-        if (n <= kOneBucket) return sort_one_bucket(keys, n, s);
-        bool done = false;
-        if (!capturing(s)) {
-            meld_status st = try_radix_sort(ctx, keys, nullptr, n, s, &done);
+        if (n > ((size_t)1 << 13) && !capturing(s)) {
+            bool done = false;
+            meld_status st =
+                try_scratch_sort(ctx, n <= meld::kRankSortMax ? SortBy::kRanks : SortBy::kRadix,
+                                 keys, nullptr, n, s, &done);
             if (done) return st;
         }
+        if (n <= kOneBucket) return sort_one_bucket(keys, n, s);
     }
     bool melded = use_melded(variant);
     if (variant == MELD_AUTO) {

@@ -119,7 +119,7 @@ def test_capture_and_fixed_options_run_the_network():
     ctx = meld.new_context(0)
     try:
         assert meld.sort_plan(n, variant="auto", ctx=ctx)["sorts_by"] == "radix"
-        assert meld.sort_plan(1 << 15, variant="auto", ctx=ctx)["sorts_by"] == "network"
+        assert meld.sort_plan(1 << 15, variant="auto", ctx=ctx)["sorts_by"] == "ranks"
         assert meld.sort_plan(n, variant="melded", ctx=ctx)["sorts_by"] == "network"
         side = torch.cuda.Stream()
         side.wait_stream(torch.cuda.current_stream())
