@@ -105,27 +105,6 @@ __global__ __launch_bounds__(NT) void bitonic_tile_kernel(SortArray a, uint32_t 
     tile_store<PAIRS, MODE, NT>(a, s, base, T);
 }
 
-// Workgroup order of the streaming passes. Consecutive workgroups go to
-// the eight XCDs in turn, each with its own L2, so tiles that lie next to
-// each other in the array would each go to another XCD. xcd_run_index gives
-// every XCD runs of 2^RUN consecutive tile indices instead: within each group
-// of 8 * 2^RUN workgroups, workgroup b's XCD (b % 8) takes 2^RUN indices in a
-// row, and the group as a whole still covers one contiguous range; a
-// workgroup in a last, partial group keeps its index (a bijection on
-// [0, count)). Merge tails (contiguous tiles) take runs of 16 tiles; the
-// tiles of consecutive middle indices of a gathered pass (array bits
-// [C, b_lo)) hold neighbouring 2^C-element pieces of every row, and take runs
-// of 4 (so each L2 streams 4 * 2^C contiguous elements per row). Both lengths
-// were the fastest of those timed on 2^28 pairs (runs of 1 .. 1024 tiles).
-constexpr uint32_t kXcdRunLogMerge = 4, kXcdRunLogGather = 2;
-template <uint32_t RUN>
-__device__ __forceinline__ uint32_t xcd_run_index(uint32_t b, uint32_t count) {
-    constexpr uint32_t mask = (8u << RUN) - 1;
-    if (b >= (count & ~mask)) return b;
-    const uint32_t j = b & mask;
-    return (b & ~mask) | ((j & 7u) << RUN) | (j >> 3);
-}
-
 // One pass of S steps (on element bits L-1 .. L-S of a tile of 2^L) of
 // phase k = 2^m, whose direction bit m lies above the tile's bits. Tile map
 // with C low bits: workgroup b's bits fill array bits [C, b_lo) and then
@@ -481,6 +460,12 @@ hipError_t launch_bitonic_merge(const SortArray &a, uint32_t log_t, uint32_t m,
                                 int32_t step_limit, int io_mode, hipStream_t stream) {
     if (a.n == 0 || step_limit == 0) return hipSuccess;
     const int32_t nsteps = step_limit < 0 ? (int32_t)log_t : step_limit;
+    // Keys alone and every step: no size is slower than by the 16-per-lane windows
+    // (whole sorts, melded form: 2^12 keys 16.8 -> 16.2 us, 2^17 55 -> 54, 2^20 120 ->
+    // 113, 2^24 716 -> 653 us, 2^28, bound by memory, 14.28 -> 14.10 ms). Smaller tiles
+    // are only taken where an option asks for them.
+    if (a.vals == nullptr && nsteps >= (int32_t)log_t && log_t >= kMergeWaveMinLog)
+        return launch_merge_wave(a, log_t, m, stream);
     if (a.vals != nullptr) return launch_merge_p<true>(a, log_t, m, nsteps, io_mode, stream);
     return launch_merge_p<false>(a, log_t, m, nsteps, io_mode, stream);
 }

@@ -123,6 +123,11 @@ constexpr uint32_t kMinGatherStepsPairs = 5;
 // (negative: all).
 hipError_t launch_bitonic_merge(const SortArray &a, uint32_t log_t, uint32_t m, int32_t step_limit, int io_mode, hipStream_t stream);
 
+// The same for keys alone and every step, 32 per lane (merge_wave.hip; log_t in
+// kMergeWaveMinLog..14).
+constexpr uint32_t kMergeWaveMinLog = 11;
+hipError_t launch_merge_wave(const SortArray &a, uint32_t log_t, uint32_t m, hipStream_t stream);
+
 // One streaming pass over all N = 2^log_n elements for the steps
 // j = 2^b_hi .. 2^b_lo of phase k = 2^m (b_hi - b_lo + 1 <= kMaxFusedSteps),
 // all in registers. At most step_limit steps run (negative: all).
