@@ -713,15 +713,16 @@ meld_status sort_one_bucket(uint32_t *keys, size_t n, hipStream_t s) {
 // One MI355X, with the copy of the input, microseconds, network / registers /
 // ranks / radix: 2^11 keys 10.8 / 10.9, 2^12 14.8 / 12.0, 2^13 21.2 / 14.3, 2^14
 // 29.3 / 23.9 / 19.5, 2^15 33 / - / 21.8 / 35, 2^16 42 / - / 25.6 / 36, 2^17 - / - / 33.6 /
-// 37; pairs with their index 49153 75 / - / - / 55, 2^17 74 / - / - / 63; pairs with
-// random payloads, twice the passes, 2^17 74 / - / - / 86, 196609 117 / - / - / 89. An
-// option that fixes how the network runs asks for the network. Ranks and radix passes not under capture: the
+// 37; pairs with their index 2^16 67 / - / - / 54, 80000 84 / - / - / 54, 2^17 81 / - /
+// - / 55; pairs with random payloads, twice the passes, 2^16 67 / - / - / 75, 80000 84
+// / - / - / 76, 2^17 81 / - / - / 77. An option that fixes how the network runs asks
+// for the network. Ranks and radix passes not under capture: the
 // recorded launches would hold the address of scratch that a later call of the
 // context may replace, where the others have none.
 enum class SortBy { kNetwork, kRegisters, kRanks, kRadix };
 SortBy auto_sort_by(const meld_ctx *ctx, bool pairs, size_t n, bool scratch) {
     if (ctx->sort_log_tile != 0 || ctx->lane_exchange >= 0) return SortBy::kNetwork;
-    if (pairs) return scratch && n > ((size_t)1 << 17) ? SortBy::kRadix : SortBy::kNetwork;
+    if (pairs) return scratch && n > ((size_t)5 << 14) ? SortBy::kRadix : SortBy::kNetwork;
     if (n <= ((size_t)1 << 11)) return SortBy::kNetwork;
     if (scratch && n > ((size_t)1 << 13))
         return n <= meld::kRankSortMax ? SortBy::kRanks : SortBy::kRadix;

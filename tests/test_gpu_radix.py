@@ -137,3 +137,13 @@ def test_capture_and_fixed_options_run_the_network():
     finally:
         torch.cuda.synchronize()
         meld.destroy_context(ctx)
+
+
+@pytest.mark.parametrize("n", [(5 << 14) - 1, 5 << 14, (5 << 14) + 1, (3 << 15) + 5])
+def test_pairs_at_the_edge_of_the_rule(n):
+    _dev()
+    by = meld.sort_plan(n, pairs=True, variant="auto", ctx=meld.context(0))["sorts_by"]
+    assert by == ("radix" if n > 5 << 14 else "network")
+    keys = workloads.keys_u32(n, n)
+    _check(keys, workloads.iota_u32(n))
+    _check(keys % np.uint32(1000), workloads.keys_u32(n + 1, n))
