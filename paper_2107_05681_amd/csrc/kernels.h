@@ -155,6 +155,11 @@ hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t n, uint32_
 hipError_t launch_bucket_sort(uint32_t *keys, uint32_t n, uint32_t log_bucket,
                               hipStream_t stream);
 
+// Sorts keys[0..n), n <= kSmallSortMax, in one workgroup with 8 or 16 keys per
+// lane (small_sort.hip). Any 4-byte alignment.
+constexpr uint32_t kSmallSortMax = 1u << 14;
+hipError_t launch_small_sort(uint32_t *keys, uint32_t n, hipStream_t stream);
+
 // Sorts keys[0..n), n <= kRankSortMax, by runs and ranks (rank_sort.hip).
 // scratch: kRankSortMax u32, 16-byte aligned.
 constexpr uint32_t kRankSortMax = 1u << 17;

@@ -694,39 +694,35 @@ SortPlan fixed_plan(const meld_ctx *ctx, bool pairs, size_t n, meld_variant v) {
     return SortPlan{plan_log_tile(ctx, pairs, log2_ceil(n)), m, m, plan_xch(ctx)};
 }
 
-// Sorts of up to so many keys take one workgroup where they may (bucket_sort.hip).
-constexpr size_t kOneBucket = (size_t)1 << 14;
-
-meld_status sort_one_bucket(uint32_t *keys, size_t n, hipStream_t s) {
-    const uint32_t log_b = std::max(6u, log2_ceil(n));
-    hipError_t e = meld::launch_bucket_sort(keys, (uint32_t)n, log_b, s);
-    return e == hipSuccess ? MELD_OK : hip_fail(e, "bucket sort launch");
+meld_status small_sort(uint32_t *keys, size_t n, hipStream_t s) {
+    hipError_t e = meld::launch_small_sort(keys, (uint32_t)n, s);
+    return e == hipSuccess ? MELD_OK : hip_fail(e, "small sort launch");
 }
 
 // How MELD_AUTO sorts n keys (with payloads) as far as the size decides:
-// kRegisters: one workgroup, above one wave's 2^11 keys, where the network's tiles
-//   need several launches or many barriers;
+// kRegisters: one workgroup with the keys in its registers (small_sort.hip), at every
+//   size that fits faster than the network's tiles in LDS;
 // kRanks: runs and ranks (rank_sort.hip), which spread the work over the chip,
 //   until the searches, n times the number of runs, take longer than radix passes;
 // kRadix: radix passes (radix.hip), above the sizes where their launches cost as
 //   much as the network's.
 // One MI355X, with the copy of the input, microseconds, network / registers /
-// ranks / radix: 2^11 keys 10.8 / 10.9, 2^12 14.8 / 12.0, 2^13 21.2 / 14.3, 2^14
-// 29.3 / 23.9 / 19.5, 2^15 33 / - / 21.8 / 35, 2^16 42 / - / 25.6 / 36, 2^17 - / - / 33.6 /
-// 37; pairs with their index 2^16 67 / - / - / 54, 80000 84 / - / - / 54, 2^17 81 / - /
-// - / 55; pairs with random payloads, twice the passes, 2^16 67 / - / - / 75, 80000 84
-// / - / - / 76, 2^17 81 / - / - / 77. An option that fixes how the network runs asks
-// for the network. Ranks and radix passes not under capture: the
-// recorded launches would hold the address of scratch that a later call of the
-// context may replace, where the others have none.
+// ranks / radix: 2^11 keys 10.8 / 8.2, 2^12 14.8 / 8.4, 2^13 21.2 / 13.1, 2^14
+// 29.3 / - / 18.6 (the kernel alone of registers 21.0), 2^15 33 / - / 20.8 / 35, 2^16
+// 42 / - / 24.8 / 36, 2^17 - / - / 32.9 / 37 (1000 keys and less: 8.4 / 8.2, bound by
+// the calls; the kernels alone 6.6 / 3.4); pairs with their index 2^16 67 / - / - / 54,
+// 80000 84 / - / - / 54, 2^17 81 / - / - / 55; pairs with random payloads, twice the
+// passes, 2^16 67 / - / - / 75, 80000 84 / - / - / 76, 2^17 81 / - / - / 77. An option
+// that fixes how the network runs asks for the network. Ranks and radix passes not
+// under capture: the recorded launches would hold the address of scratch that a later
+// call of the context may replace, where the others have none.
 enum class SortBy { kNetwork, kRegisters, kRanks, kRadix };
 SortBy auto_sort_by(const meld_ctx *ctx, bool pairs, size_t n, bool scratch) {
     if (ctx->sort_log_tile != 0 || ctx->lane_exchange >= 0) return SortBy::kNetwork;
     if (pairs) return scratch && n > ((size_t)5 << 14) ? SortBy::kRadix : SortBy::kNetwork;
-    if (n <= ((size_t)1 << 11)) return SortBy::kNetwork;
     if (scratch && n > ((size_t)1 << 13))
         return n <= meld::kRankSortMax ? SortBy::kRanks : SortBy::kRadix;
-    return n <= kOneBucket ? SortBy::kRegisters : SortBy::kNetwork;
+    return n <= meld::kSmallSortMax ? SortBy::kRegisters : SortBy::kNetwork;
 }
 
 // A sort by ranks or radix passes on the context's scratch; *done is false where
@@ -1321,7 +1317,7 @@ meld_status meld_sort_u32(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size
             if (done) return st;
             by = auto_sort_by(ctx, pairs, n, false);
         }
-        if (by == SortBy::kRegisters) return sort_one_bucket(keys, n, s);
+        if (by == SortBy::kRegisters) return small_sort(keys, n, s);
     }
     SortPlan plan = fixed_plan(ctx, payload != nullptr, n, variant);
     if (variant == MELD_AUTO) {
@@ -1526,7 +1522,7 @@ meld_status meld_merge_sort_u32(meld_ctx *ctx, uint32_t *keys, size_t n, int64_t
                                  keys, nullptr, n, s, &done);
             if (done) return st;
         }
-        if (n <= kOneBucket) return sort_one_bucket(keys, n, s);
+        if (n <= meld::kSmallSortMax) return small_sort(keys, n, s);
     }
     bool melded = use_melded(variant);
     if (variant == MELD_AUTO) {

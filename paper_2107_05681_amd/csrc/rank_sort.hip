@@ -16,7 +16,8 @@ namespace {
 constexpr uint32_t kRankPad = 0xFFFFFFFFu;
 constexpr int kRunLog = 13;
 constexpr uint32_t kRun = 1u << kRunLog;
-constexpr int kRunThreads = kRun / kWaveE;
+constexpr int kRunE = 16;
+constexpr int kRunThreads = wave_group_threads<kRunE, kRunLog>();
 constexpr int kRankThreads = 256;
 
 // A run per workgroup, written whole: with the padding behind the last key, and in
@@ -27,27 +28,22 @@ __global__ __launch_bounds__(kRunThreads) void rank_runs_kernel(const uint32_t *
     __shared__ __align__(16) uint32_t s[wave_lds_words(kRun)];
     const WaveLane w = wave_lane();
     const uint32_t t = threadIdx.x, tile = blockIdx.x * kRun;
-    uint32_t e[kWaveE];
+    uint32_t e[kRunE];
     if (tile + kRun <= n) {
 #pragma unroll
-        for (int r = 0; r < kWaveE; ++r) e[r] = keys[tile + r * kRunThreads + t];
+        for (int r = 0; r < kRunE; ++r) e[r] = keys[tile + r * kRunThreads + t];
     } else {
 #pragma unroll
-        for (int r = 0; r < kWaveE; ++r) {
+        for (int r = 0; r < kRunE; ++r) {
             const uint32_t p = tile + r * kRunThreads + t;
             e[r] = p < n ? keys[p] : kRankPad;
         }
     }
-    if (tile < n) wave_sort<kRunLog>(e, s, w);
-    uint32_t *own = s + t / 64 * wave_lds_words(kWaveTile);
-    wave_to_lds<true>(e, own, w);
-    __builtin_amdgcn_wave_barrier();
-    uint32_t *to = runs + tile + (t & ~63u) * kWaveE;
+    if (tile < n) wave_group_sort<kRunLog>(e, s, w);
+    uint4 *to = reinterpret_cast<uint4 *>(runs + tile + wave_group_row<kRunE>(w, true));
 #pragma unroll
-    for (int c = 0; c < kWaveE / 4; ++c) {
-        const uint32_t i = (c * 64 + (t & 63)) * 4;
-        *reinterpret_cast<uint4 *>(to + i) = *reinterpret_cast<const uint4 *>(own + wave_phys(i));
-    }
+    for (int c = 0; c < kRunE; c += 4)
+        to[c / 4] = make_uint4(e[c], e[c + 1], e[c + 2], e[c + 3]);
 }
 
 // One thread per key; the 256 keys of a workgroup are neighbours in one run, so

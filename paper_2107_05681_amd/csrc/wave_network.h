@@ -29,8 +29,16 @@ namespace {
 constexpr int kWaveE = 32;               // keys per lane
 constexpr uint32_t kWaveTile = 64 * kWaveE;
 
+// Register bits of a lane that holds E keys (32, or 16 or 8 where a small array is
+// spread over more lanes; the functions below take the number from the array, and
+// their element bits count from it: B .. B + 5 are the lane).
+template <int E>
+constexpr int wave_bits() {
+    return E == 32 ? 5 : E == 16 ? 4 : 3;
+}
+
 struct WaveLane {
-    uint32_t id;      // bits 5 .. 10 of the lane's elements
+    uint32_t id;      // the lane bits of the lane's elements (bits 5 .. 10 of 32 each)
     uint32_t keep[4];  // 0 where the lane is the lower end of lane bit i, else ~0
 };
 
@@ -52,10 +60,10 @@ __device__ __forceinline__ uint32_t median(uint32_t x, uint32_t y, uint32_t z) {
 }
 
 // Register steps on bit Q.
-template <int Q>
-__device__ __forceinline__ void wave_reg_step(uint32_t (&e)[kWaveE]) {
+template <int Q, int E>
+__device__ __forceinline__ void wave_reg_step(uint32_t (&e)[E]) {
 #pragma unroll
-    for (int r = 0; r < kWaveE; ++r)
+    for (int r = 0; r < E; ++r)
         if ((r & (1 << Q)) == 0) {
             const uint32_t x = e[r], y = e[r | (1 << Q)];
             e[r] = x < y ? x : y;
@@ -64,20 +72,21 @@ __device__ __forceinline__ void wave_reg_step(uint32_t (&e)[kWaveE]) {
 }
 
 // Steps on register bits TOP .. 0.
-template <int TOP>
-__device__ __forceinline__ void wave_reg_steps(uint32_t (&e)[kWaveE]) {
+template <int TOP, int E>
+__device__ __forceinline__ void wave_reg_steps(uint32_t (&e)[E]) {
     if constexpr (TOP >= 0) {
         wave_reg_step<TOP>(e);
         wave_reg_steps<TOP - 1>(e);
     }
 }
 
-// Phases 2^1 .. 2^4: bit M of the register index is the direction.
-template <int M, int Q>
-__device__ __forceinline__ void wave_first_phases(uint32_t (&e)[kWaveE]) {
-    if constexpr (M <= 4) {
+// Phases 2^1 .. 2^(B-1), B register bits: bit M of the register index is the
+// direction.
+template <int M, int Q, int E>
+__device__ __forceinline__ void wave_first_phases(uint32_t (&e)[E]) {
+    if constexpr (M < wave_bits<E>()) {
 #pragma unroll
-        for (int r = 0; r < kWaveE; ++r)
+        for (int r = 0; r < E; ++r)
             if ((r & (1 << Q)) == 0) {
                 const uint32_t x = e[r], y = e[r | (1 << Q)];
                 const uint32_t mn = x < y ? x : y, mx = x < y ? y : x;
@@ -91,78 +100,81 @@ __device__ __forceinline__ void wave_first_phases(uint32_t (&e)[kWaveE]) {
     }
 }
 
-// The step on lane bit B (element bit 5 + B), B <= 3.
-template <int B>
-__device__ __forceinline__ void wave_lane_step(uint32_t (&e)[kWaveE], uint32_t keep) {
+// The step on lane bit B, B <= 3.
+template <int B, int E>
+__device__ __forceinline__ void wave_lane_step(uint32_t (&e)[E], uint32_t keep) {
     constexpr int ctrl = B == 0 ? 0xB1 : B == 1 ? 0x4E : B == 2 ? 0x141 : 0x128;
 #pragma unroll
-    for (int r = 0; r < kWaveE; ++r)
+    for (int r = 0; r < E; ++r)
         e[r] = median(e[r], (uint32_t)__builtin_amdgcn_mov_dpp((int)e[r], ctrl, 0xF, 0xF, true),
                       keep);
 }
 
-// Trades lane bit 4 (SWAP32: 5) for register bit 4.
-template <bool SWAP32>
-__device__ __forceinline__ void wave_trade(uint32_t (&e)[kWaveE]) {
+// Trades lane bit 4 (SWAP32: 5) for the top register bit.
+template <bool SWAP32, int E>
+__device__ __forceinline__ void wave_trade(uint32_t (&e)[E]) {
 #pragma unroll
-    for (int r = 0; r < kWaveE / 2; ++r) {
+    for (int r = 0; r < E / 2; ++r) {
         if constexpr (SWAP32) {
-            const auto p = __builtin_amdgcn_permlane32_swap(e[r], e[r + kWaveE / 2], false, false);
+            const auto p = __builtin_amdgcn_permlane32_swap(e[r], e[r + E / 2], false, false);
             e[r] = p[0];
-            e[r + kWaveE / 2] = p[1];
+            e[r + E / 2] = p[1];
         } else {
-            const auto p = __builtin_amdgcn_permlane16_swap(e[r], e[r + kWaveE / 2], false, false);
+            const auto p = __builtin_amdgcn_permlane16_swap(e[r], e[r + E / 2], false, false);
             e[r] = p[0];
-            e[r + kWaveE / 2] = p[1];
+            e[r + E / 2] = p[1];
         }
     }
 }
 
-// Steps on element bits TOP .. 0 of a wave (TOP <= 10). TOP = 10 takes three
-// trades for its two upper bits instead of four and leaves bits 9 and 10 in
-// each other's place: bit 9 is lane bit 5 then, bit 10 lane bit 4.
-template <int TOP>
-__device__ __forceinline__ void wave_steps(uint32_t (&e)[kWaveE], const WaveLane &w) {
-    if constexpr (TOP == 10) {
+// Steps on element bits TOP .. 0 of a wave, B register bits. TOP = B + 5 takes
+// three trades for its two upper bits instead of four and leaves bits B + 4 and
+// B + 5 in each other's place: bit B + 4 is lane bit 5 then, bit B + 5 lane bit 4.
+template <int TOP, int E>
+__device__ __forceinline__ void wave_steps(uint32_t (&e)[E], const WaveLane &w) {
+    constexpr int B = wave_bits<E>();
+    static_assert(TOP <= B + 5, "above the wave");
+    if constexpr (TOP == B + 5) {
         wave_trade<true>(e);
-        wave_reg_step<4>(e);
+        wave_reg_step<B - 1>(e);
         wave_trade<false>(e);
-        wave_reg_step<4>(e);
+        wave_reg_step<B - 1>(e);
         wave_trade<true>(e);
-        wave_steps<8>(e, w);
-    } else if constexpr (TOP == 9) {
+        wave_steps<B + 3>(e, w);
+    } else if constexpr (TOP == B + 4) {
         wave_trade<false>(e);
-        wave_reg_step<4>(e);
+        wave_reg_step<B - 1>(e);
         wave_trade<false>(e);
-        wave_steps<8>(e, w);
-    } else if constexpr (TOP >= 5) {
-        wave_lane_step<TOP - 5>(e, w.keep[TOP - 5]);
+        wave_steps<B + 3>(e, w);
+    } else if constexpr (TOP >= B) {
+        wave_lane_step<TOP - B>(e, w.keep[TOP - B]);
         wave_steps<TOP - 1>(e, w);
     } else {
         wave_reg_steps<TOP>(e);
     }
 }
 
-__device__ __forceinline__ void wave_flip(uint32_t (&e)[kWaveE], uint32_t mask) {
+template <int E>
+__device__ __forceinline__ void wave_flip(uint32_t (&e)[E], uint32_t mask) {
 #pragma unroll
-    for (int r = 0; r < kWaveE; ++r) e[r] ^= mask;
+    for (int r = 0; r < E; ++r) e[r] ^= mask;
 }
 
 // The complement of phase 2^M of a sort whose last phase is 2^LAST: all ones
-// where bit M of the elements is set, nothing in the last phase. high: bits 5
+// where bit M of the elements is set, nothing in the last phase. high: bits B
 // and up of the lane's elements.
-template <int M, int LAST>
+template <int M, int LAST, int B = 5>
 __device__ __forceinline__ uint32_t wave_down(uint32_t high) {
-    return M < LAST ? (uint32_t)-(int32_t)((high >> (M - 5)) & 1u) : 0u;
+    return M < LAST ? (uint32_t)-(int32_t)((high >> (M - B)) & 1u) : 0u;
 }
 
-// Phases 2^M .. 2^min(LAST, 11) on keys already complemented for phase 2^M.
-template <int M, int LAST>
-__device__ __forceinline__ void wave_phases(uint32_t (&e)[kWaveE], const WaveLane &w,
-                                            uint32_t high) {
+// Phases 2^M .. 2^min(LAST, B + 6) on keys already complemented for phase 2^M.
+template <int M, int LAST, int E>
+__device__ __forceinline__ void wave_phases(uint32_t (&e)[E], const WaveLane &w, uint32_t high) {
+    constexpr int B = wave_bits<E>();
     wave_steps<M - 1>(e, w);
-    if constexpr (M < LAST && M < 11) {
-        wave_flip(e, wave_down<M, LAST>(high) ^ wave_down<M + 1, LAST>(high));
+    if constexpr (M < LAST && M < B + 6) {
+        wave_flip(e, wave_down<M, LAST, B>(high) ^ wave_down<M + 1, LAST, B>(high));
         wave_phases<M + 1, LAST>(e, w, high);
     }
 }
@@ -262,6 +274,79 @@ __device__ __forceinline__ void wave_sort(uint32_t (&e)[kWaveE], uint32_t *s, co
     wave_flip(e, wave_down<5, LOG>(high));
     wave_phases<5, LOG>(e, w, high);
     wave_cross_phases<12, LOG>(e, s, w, high);
+}
+
+// The same with E = 8 or 16 keys per lane, which gives each SIMD more waves to
+// hide the chain of steps behind.
+template <int E, int LOG>
+constexpr int wave_group_threads() {
+    return LOG > wave_bits<E>() + 6 ? (1 << LOG) / E : 64;
+}
+
+// The lane's first element in the workgroup. traded: the two upper lane bits are in
+// each other's place.
+template <int E>
+__device__ __forceinline__ uint32_t wave_group_row(const WaveLane &w, bool traded) {
+    const uint32_t id = traded ? (w.id & 15u) | ((w.id & 16u) << 1) | ((w.id & 32u) >> 1) : w.id;
+    return ((threadIdx.x & ~63u) | id) * E;
+}
+
+// Phases 2^M .. 2^LOG above a wave's on keys complemented for phase 2^(M-1): for the
+// steps across waves every lane takes one piece of each wave's keys.
+template <int M, int LOG, int E>
+__device__ __forceinline__ void wave_group_cross(uint32_t (&e)[E], uint32_t *s, const WaveLane &w,
+                                                 uint32_t high) {
+    if constexpr (M <= LOG) {
+        constexpr int B = wave_bits<E>(), TOP = B + 5;
+        constexpr int WB = LOG - TOP - 1;  // wave bits
+        constexpr int GB = B - WB;         // low element bits that stay registers
+        static_assert(GB >= 0, "one exchange per phase");
+        wave_flip(e, wave_down<M - 1, LOG, B>(high) ^ wave_down<M, LOG, B>(high));
+        uint4 *from = reinterpret_cast<uint4 *>(s + wave_phys(wave_group_row<E>(w, true)));
+#pragma unroll
+        for (int c = 0; c < E / 4; ++c)
+            from[c] = make_uint4(e[4 * c], e[4 * c + 1], e[4 * c + 2], e[4 * c + 3]);
+        __syncthreads();
+        uint32_t *p = s + wave_phys((uint32_t)threadIdx.x << GB);
+        auto at = [&](int r) -> uint32_t & {
+            return p[wave_phys((uint32_t)(r >> GB) << (TOP + 1)) + (r & ((1 << GB) - 1))];
+        };
+#pragma unroll
+        for (int r = 0; r < E; ++r) e[r] = at(r);
+        if constexpr (M - TOP >= 5) wave_reg_step<GB + 3>(e);
+        if constexpr (M - TOP >= 4) wave_reg_step<GB + 2>(e);
+        if constexpr (M - TOP >= 3) wave_reg_step<GB + 1>(e);
+        wave_reg_step<GB>(e);
+#pragma unroll
+        for (int r = 0; r < E; ++r) at(r) = e[r];
+        __syncthreads();
+        const uint4 *to = reinterpret_cast<const uint4 *>(s + wave_phys(wave_group_row<E>(w, false)));
+#pragma unroll
+        for (int c = 0; c < E / 4; ++c) {
+            const uint4 v = to[c];
+            e[4 * c] = v.x;
+            e[4 * c + 1] = v.y;
+            e[4 * c + 2] = v.z;
+            e[4 * c + 3] = v.w;
+        }
+        // The next phase's writes go to the lane's own wave's keys, which only that
+        // wave reads until the next barrier.
+        wave_steps<TOP>(e, w);
+        wave_group_cross<M + 1, LOG>(e, s, w, high);
+    }
+}
+
+// Sorts 2^LOG keys of a workgroup from any order into rows of E per lane
+// (wave_group_row; traded for whole waves). s: 2^LOG elements of LDS
+// (wave_lds_words) where there is more than one wave.
+template <int LOG, int E>
+__device__ __forceinline__ void wave_group_sort(uint32_t (&e)[E], uint32_t *s, const WaveLane &w) {
+    constexpr int B = wave_bits<E>();
+    const uint32_t high = (threadIdx.x & ~63u) | w.id;
+    wave_first_phases<1, 0>(e);
+    wave_flip(e, wave_down<B, LOG, B>(high));
+    wave_phases<B, LOG>(e, w, high);
+    wave_group_cross<B + 7, LOG>(e, s, w, high);
 }
 
 }  // namespace
