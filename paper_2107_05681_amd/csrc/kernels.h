@@ -161,8 +161,10 @@ constexpr uint32_t kSmallSortMax = 1u << 14;
 hipError_t launch_small_sort(uint32_t *keys, uint32_t n, hipStream_t stream);
 
 // Sorts keys[0..n), n <= kRankSortMax, by runs and ranks (rank_sort.hip).
-// scratch: kRankSortMax u32, 16-byte aligned.
-constexpr uint32_t kRankSortMax = 1u << 17;
+// scratch: kRankScratchWords u32, 16-byte aligned.
+// Up to kRankSortMin keys one workgroup is faster.
+constexpr uint32_t kRankSortMin = 1u << 12, kRankSortMax = 1u << 17;
+constexpr uint32_t kRankScratchWords = kRankSortMax + kRankSortMax / 8;
 hipError_t launch_rank_sort(uint32_t *keys, uint32_t n, uint32_t *scratch, hipStream_t stream);
 
 hipError_t launch_fill_u32(uint32_t *p, uint32_t value, size_t count, hipStream_t stream);

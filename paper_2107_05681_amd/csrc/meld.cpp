@@ -707,10 +707,10 @@ meld_status small_sort(uint32_t *keys, size_t n, hipStream_t s) {
 // kRadix: radix passes (radix.hip), above the sizes where their launches cost as
 //   much as the network's.
 // One MI355X, with the copy of the input, microseconds, network / registers /
-// ranks / radix: 2^11 keys 10.8 / 8.2, 2^12 14.8 / 8.4, 2^13 21.2 / 13.1, 2^14
-// 29.3 / - / 18.6 (the kernel alone of registers 21.0), 2^15 33 / - / 20.8 / 35, 2^16
-// 42 / - / 24.8 / 36, 2^17 - / - / 32.9 / 37 (1000 keys and less: 8.4 / 8.2, bound by
-// the calls; the kernels alone 6.6 / 3.4); pairs with their index 2^16 67 / - / - / 54,
+// ranks / radix: 1000 keys 8.4 / 8.2 (bound by the calls; the kernels alone 6.6 / 3.4),
+// 2^11 10.8 / 8.2, 2^12 14.8 / 8.4, 2^13 21.2 / 13.1 / 10.9, 2^14 29.3 / - / 11.2 (the
+// kernel alone of registers 21), 2^15 33 / - / 11.3 / 35, 2^16 42 / - / 14.6 / 36, 2^17
+// - / - / 23.9 / 37; pairs with their index 2^16 67 / - / - / 54,
 // 80000 84 / - / - / 54, 2^17 81 / - / - / 55; pairs with random payloads, twice the
 // passes, 2^16 67 / - / - / 75, 80000 84 / - / - / 76, 2^17 81 / - / - / 77. An option
 // that fixes how the network runs asks for the network. Ranks and radix passes not
@@ -720,7 +720,7 @@ enum class SortBy { kNetwork, kRegisters, kRanks, kRadix };
 SortBy auto_sort_by(const meld_ctx *ctx, bool pairs, size_t n, bool scratch) {
     if (ctx->sort_log_tile != 0 || ctx->lane_exchange >= 0) return SortBy::kNetwork;
     if (pairs) return scratch && n > ((size_t)5 << 14) ? SortBy::kRadix : SortBy::kNetwork;
-    if (scratch && n > ((size_t)1 << 13))
+    if (scratch && n > meld::kRankSortMin)
         return n <= meld::kRankSortMax ? SortBy::kRanks : SortBy::kRadix;
     return n <= meld::kSmallSortMax ? SortBy::kRegisters : SortBy::kNetwork;
 }
@@ -730,7 +730,7 @@ SortBy auto_sort_by(const meld_ctx *ctx, bool pairs, size_t n, bool scratch) {
 meld_status try_scratch_sort(meld_ctx *ctx, SortBy by, uint32_t *keys, uint32_t *payload, size_t n,
                              hipStream_t s, bool *done) {
     const bool ranks = by == SortBy::kRanks;
-    const size_t words = ranks ? (size_t)meld::kRankSortMax
+    const size_t words = ranks ? (size_t)meld::kRankScratchWords
                                : meld::radix_scratch_words((uint32_t)n, payload != nullptr);
     *done = ensure_words(&ctx->merge_buf, &ctx->merge_words, words, "sort scratch") == MELD_OK;
     if (!*done) return MELD_OK;
@@ -1511,11 +1511,11 @@ meld_status meld_merge_sort_u32(meld_ctx *ctx, uint32_t *keys, size_t n, int64_t
                     ctx->device);
     const hipStream_t s = static_cast<hipStream_t>(stream);
     // All passes: only the sorted array counts (with the copy of the input, against
-    // the faster form of the merge sort, microseconds: 1000 keys 10.3 / 17.6, 2^14
-    // 19.5 / 47.5, 2^15 21.8 / 62, 2^20 55 / 135, 2^24 228 / 696). Above 2^14 keys under
+    // the faster form of the merge sort, microseconds: 1000 keys 8.2 / 17.6, 2^14
+    // 11.2 / 47.5, 2^15 11.3 / 62, 2^20 55 / 135, 2^24 228 / 696). Above 2^14 keys under
     // capture, and without the memory for the scratch, the merge passes.
     if (variant == MELD_AUTO && max_passes < 0) {
-        if (n > ((size_t)1 << 13) && !capturing(s)) {
+        if (n > meld::kRankSortMin && !capturing(s)) {
             bool done = false;
             meld_status st =
                 try_scratch_sort(ctx, n <= meld::kRankSortMax ? SortBy::kRanks : SortBy::kRadix,

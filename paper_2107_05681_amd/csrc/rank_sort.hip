@@ -1,11 +1,15 @@
-// Sort of 2^13 .. 2^17 keys in two launches: runs of 2^13 by a workgroup each
+// Sort of 2^12 .. 2^17 keys in two launches: runs by a workgroup each
 // (wave_network.h), then every key to its rank: its place in its own run plus, by
-// binary search, the number of keys before it in each other run. The searches of a
-// key do not depend on each other, so that all of them wait for memory together.
-// Equal keys of an earlier run come before, of a later run after. The searches grow
-// with n times the number of runs, which is why larger arrays go through radix
-// passes; runs of 2^11, 2 us faster to sort, would make them four times as many
-// (2^16 keys: 40 us).
+// search, the number of keys before it in each other run. Equal keys of an earlier run
+// come before, of a later run after. A search would be a chain of a round trip to
+// memory per level (eleven to thirteen, 0.6 us each); the runs leave a sample of every
+// 8 or 16 keys, which fits in LDS for all runs, and what is left of a search is one
+// round trip for the keys of one sample.
+//
+// The searches grow with n times the number of runs, the runs' sort with their length,
+// hence longer runs for more keys. Microseconds, runs + places: 2^14 keys in 8 runs
+// 4.9 + 3.8 (2 runs searched in memory: 12.2 + 5.3), 2^15 in 16 runs 4.9 + 5.3, 2^16 in
+// 16 runs 7.2 + 7.3 (8 runs searched in memory: 12.2 + 11.7), 2^17 in 16 runs 12.8 + 11.1.
 #include "kernels.h"
 #include "wave_network.h"
 
@@ -14,92 +18,151 @@ namespace meld {
 namespace {
 
 constexpr uint32_t kRankPad = 0xFFFFFFFFu;
-constexpr int kRunLog = 13;
-constexpr uint32_t kRun = 1u << kRunLog;
-constexpr int kRunE = 16;
-constexpr int kRunThreads = wave_group_threads<kRunE, kRunLog>();
-constexpr int kRankThreads = 256;
+
+// Keys per lane of a run's sort, and how many keys of a run one sample stands for.
+template <int LOG>
+constexpr int run_e() {
+    return LOG > 12 ? 16 : 8;
+}
+template <int LOG>
+constexpr uint32_t sample() {
+    return LOG > 11 ? 8 : 16;
+}
 
 // A run per workgroup, written whole: with the padding behind the last key, and in
-// the runs past it.
-__global__ __launch_bounds__(kRunThreads) void rank_runs_kernel(const uint32_t *__restrict__ keys,
-                                                                uint32_t n,
-                                                                uint32_t *__restrict__ runs) {
-    __shared__ __align__(16) uint32_t s[wave_lds_words(kRun)];
+// the runs past it. The last of every sample() keys goes to samples too.
+template <int LOG>
+__global__ __launch_bounds__((wave_group_threads<run_e<LOG>(), LOG>())) void rank_runs_kernel(
+    const uint32_t *__restrict__ keys, uint32_t n, uint32_t *__restrict__ runs,
+    uint32_t *__restrict__ samples) {
+    constexpr int E = run_e<LOG>(), T = wave_group_threads<E, LOG>();
+    constexpr uint32_t RUN = 1u << LOG;
+    __shared__ __align__(16) uint32_t s[wave_lds_words(RUN)];
     const WaveLane w = wave_lane();
-    const uint32_t t = threadIdx.x, tile = blockIdx.x * kRun;
-    uint32_t e[kRunE];
-    if (tile + kRun <= n) {
+    const uint32_t t = threadIdx.x, tile = blockIdx.x * RUN;
+    uint32_t e[E];
+    if (tile + RUN <= n) {
 #pragma unroll
-        for (int r = 0; r < kRunE; ++r) e[r] = keys[tile + r * kRunThreads + t];
+        for (int r = 0; r < E; ++r) e[r] = keys[tile + r * T + t];
     } else {
 #pragma unroll
-        for (int r = 0; r < kRunE; ++r) {
-            const uint32_t p = tile + r * kRunThreads + t;
+        for (int r = 0; r < E; ++r) {
+            const uint32_t p = tile + r * T + t;
             e[r] = p < n ? keys[p] : kRankPad;
         }
     }
-    if (tile < n) wave_group_sort<kRunLog>(e, s, w);
-    uint4 *to = reinterpret_cast<uint4 *>(runs + tile + wave_group_row<kRunE>(w, true));
+    if (tile < n) wave_group_sort<LOG>(e, s, w);
+    const uint32_t row = tile + wave_group_row<E>(w, true);
+    uint4 *to = reinterpret_cast<uint4 *>(runs + row);
 #pragma unroll
-    for (int c = 0; c < kRunE; c += 4)
+    for (int c = 0; c < E; c += 4)
         to[c / 4] = make_uint4(e[c], e[c + 1], e[c + 2], e[c + 3]);
+    constexpr uint32_t S = sample<LOG>();
+    if constexpr ((uint32_t)E >= S) {
+#pragma unroll
+        for (uint32_t r = S - 1; r < E; r += S) samples[(row + r) / S] = e[r];
+    } else if (row % S + E == S) {
+        samples[row / S] = e[E - 1];
+    }
 }
 
-// One thread per key; the 256 keys of a workgroup are neighbours in one run, so
-// that their probes fall on few cache lines. Bound by the fourteen round trips to
-// memory of a search, 0.6 us each, and by the address path.
-template <int RUNS>
-__global__ __launch_bounds__(kRankThreads) void rank_place_kernel(
-    const uint32_t *__restrict__ runs, uint32_t n, uint32_t *__restrict__ keys) {
-    const uint32_t i = blockIdx.x * kRankThreads + threadIdx.x;
-    const uint32_t own = blockIdx.x * kRankThreads >> kRunLog;
+// K neighbours in one run per workgroup, so that their probes fall on few cache lines
+// and LDS words, and a thread for each of them and a share of the runs: the shares keep
+// every compute unit busy where there are few keys, and shorten the chain of a thread
+// (2^16 keys, 256 to a workgroup: 18.6 us with the copy of the input without shares, 15.1
+// with two, 14.6 for 64 keys with eight).
+template <int LOG, int RUNS, int K, int SHARES>
+__global__ __launch_bounds__(K *SHARES) void rank_place_kernel(
+    const uint32_t *__restrict__ runs, const uint32_t *__restrict__ samples, uint32_t n,
+    uint32_t *__restrict__ keys) {
+    constexpr uint32_t RUN = 1u << LOG, S = sample<LOG>(), PER = RUN / S,
+                       T = K * SHARES;
+    constexpr int G = RUNS / SHARES;
+    __shared__ __align__(16) uint32_t s[RUNS * PER];
+    __shared__ uint32_t part[SHARES * K];
+    const uint32_t t = threadIdx.x, i = blockIdx.x * K + t % K;
+    const uint32_t own = blockIdx.x * K >> LOG;
+    const uint32_t first = __builtin_amdgcn_readfirstlane(t / K * G);  // of the share's runs
     const uint32_t x = runs[i];
-    uint32_t pos[RUNS], y[RUNS];
 #pragma unroll
-    for (int r = 0; r < RUNS; ++r) pos[r] = 0;
+    for (uint32_t c = 0; c < RUNS * PER; c += T * 4)
+        if (RUNS * PER % (T * 4) == 0 || c + t * 4 < RUNS * PER)
+            *reinterpret_cast<uint4 *>(s + c + t * 4) =
+                *reinterpret_cast<const uint4 *>(samples + c + t * 4);
+    __syncthreads();
     // A key of an earlier run stands before an equal one, of a later run after.
-    auto advance = [&](uint32_t by) {
+    auto before = [&](int r, uint32_t y) { return first + r < own ? y <= x : y < x; };
+    uint32_t pos[G];
 #pragma unroll
-        for (int r = 0; r < RUNS; ++r)
-            if ((uint32_t)r < own ? y[r] <= x : y[r] < x) pos[r] += by;
-    };
+    for (int r = 0; r < G; ++r) pos[r] = 0;
 #pragma unroll
-    for (uint32_t half = kRun / 2; half != 0; half >>= 1) {
+    for (uint32_t half = PER / 2; half != 0; half >>= 1) {
+        uint32_t y[G];
 #pragma unroll
-        for (int r = 0; r < RUNS; ++r) y[r] = runs[((uint32_t)r << kRunLog) + pos[r] + half - 1];
-        advance(half);
+        for (int r = 0; r < G; ++r) y[r] = s[(first + r) * PER + pos[r] + half - 1];
+#pragma unroll
+        for (int r = 0; r < G; ++r)
+            if (before(r, y[r])) pos[r] += half;
     }
-    // Places 0 .. 2^13 - 1 so far; one key of the run is left to look at.
+    uint4 y[G][S / 4];
 #pragma unroll
-    for (int r = 0; r < RUNS; ++r) y[r] = runs[((uint32_t)r << kRunLog) + pos[r]];
-    advance(1);
+    for (int r = 0; r < G; ++r)
+#pragma unroll
+        for (int c = 0; c < (int)S / 4; ++c)
+            y[r][c] = *reinterpret_cast<const uint4 *>(runs + (first + r) * RUN +
+                                                       pos[r] * S + 4 * c);
+    __builtin_amdgcn_sched_barrier(0);  // every load before the first wait
     uint32_t rank = 0;
 #pragma unroll
-    for (int r = 0; r < RUNS; ++r) rank += (uint32_t)r == own ? i & (kRun - 1) : pos[r];
+    for (int r = 0; r < G; ++r) {
+        uint32_t at = pos[r] * S;
+#pragma unroll
+        for (int c = 0; c < (int)S / 4; ++c)
+            at += (uint32_t)before(r, y[r][c].x) + before(r, y[r][c].y) +
+                  before(r, y[r][c].z) + before(r, y[r][c].w);
+        rank += first + r == own ? i & (RUN - 1) : at;
+    }
+    if constexpr (SHARES > 1) {
+        part[t] = rank;
+        __syncthreads();
+        if (t >= K) return;
+#pragma unroll
+        for (int c = 1; c < SHARES; ++c) rank += part[c * K + t];
+    }
     if (i < n) keys[rank] = x;
 }
 
-template <int RUNS>
+template <int LOG, int RUNS, int K, int SHARES>
 void launch_ranks(uint32_t *keys, uint32_t n, uint32_t *runs, hipStream_t stream) {
-    hipLaunchKernelGGL(rank_runs_kernel, dim3(RUNS), dim3(kRunThreads), 0, stream,
-                       (const uint32_t *)keys, n, runs);
-    hipLaunchKernelGGL(rank_place_kernel<RUNS>, dim3(blocks_for(n, kRankThreads)),
-                       dim3(kRankThreads), 0, stream, (const uint32_t *)runs, n, keys);
+    uint32_t *samples = runs + ((uint32_t)RUNS << LOG);
+    hipLaunchKernelGGL(rank_runs_kernel<LOG>, dim3(RUNS),
+                       dim3(wave_group_threads<run_e<LOG>(), LOG>()), 0, stream,
+                       (const uint32_t *)keys, n, runs, samples);
+    hipLaunchKernelGGL((rank_place_kernel<LOG, RUNS, K, SHARES>), dim3(blocks_for(n, K)),
+                       dim3(K * SHARES), 0, stream, (const uint32_t *)runs,
+                       (const uint32_t *)samples, n, keys);
 }
 
 }  // namespace
 
 hipError_t launch_rank_sort(uint32_t *keys, uint32_t n, uint32_t *scratch, hipStream_t stream) {
     if (n > kRankSortMax) return hipErrorInvalidValue;
-    if (n <= 2 * kRun)
-        launch_ranks<2>(keys, n, scratch, stream);
-    else if (n <= 4 * kRun)
-        launch_ranks<4>(keys, n, scratch, stream);
-    else if (n <= 8 * kRun)
-        launch_ranks<8>(keys, n, scratch, stream);
+    // With the copy of the input, microseconds, 2^11 / 2^12 / 2^13 keys to a run (64 keys
+    // to a workgroup, two runs to a thread): 2^14 10.0 / 11.6 / 16.2, 2^15 10.7 / 12.1 /
+    // 16.9, 2^16 15.6 / 14.6 / 18.3, 80000 22.0 / 20.5 (24 runs: 18.5) / 23.0, 2^17 25.7 /
+    // 26.5 / 27.1 (four runs to a thread and 256 keys: 23.8).
+    if (n <= 4u << 11)
+        launch_ranks<11, 4, 64, 2>(keys, n, scratch, stream);
+    else if (n <= 8u << 11)
+        launch_ranks<11, 8, 64, 4>(keys, n, scratch, stream);
+    else if (n <= 16u << 11)
+        launch_ranks<11, 16, 64, 8>(keys, n, scratch, stream);
+    else if (n <= 16u << 12)
+        launch_ranks<12, 16, 64, 8>(keys, n, scratch, stream);
+    else if (n <= 24u << 12)
+        launch_ranks<12, 24, 64, 12>(keys, n, scratch, stream);
     else
-        launch_ranks<16>(keys, n, scratch, stream);
+        launch_ranks<13, 16, 256, 4>(keys, n, scratch, stream);
     return hipGetLastError();
 }
 

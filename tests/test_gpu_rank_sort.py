@@ -1,4 +1,4 @@
-"""MELD_AUTO sorts of 2^13 + 1 .. 2^17 keys (runs and ranks) against the oracle.
+"""MELD_AUTO sorts of 2^12 + 1 .. 2^17 keys (runs and ranks) against the oracle.
 
 Bar: bit-exact. Sizes at the edges of a run and of the numbers of runs the kernels are
 built for; ties within and across runs, the padding's value, sorted and reversed input;
@@ -15,9 +15,9 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 meld = pytest.importorskip("paper_2107_05681_amd")
 
-SIZES = [(1 << 13) + 1, 10_000, (1 << 14) - 1, 1 << 14, (1 << 14) + 1, 20_480, (1 << 15) - 3,
+SIZES = [(1 << 12) + 1, 5000, 6144, (1 << 13) - 1, 1 << 13, (1 << 13) + 1, 10_000, (1 << 14) - 1, 1 << 14, (1 << 14) + 1, 20_480, (1 << 15) - 3,
          1 << 15, (1 << 15) + 1, 50_001, (1 << 16) - 1, 1 << 16, (1 << 16) + 1, 90_113,
-         (1 << 17) - 8191, 1 << 17]
+         98_303, 98_304, 98_305, (1 << 17) - 8191, 1 << 17]
 
 
 def _sort(keys, ctx, sort):
@@ -45,7 +45,7 @@ def test_sizes_and_orders():
                 k = np.ascontiguousarray(k)
                 assert np.array_equal(_sort(k, ctx, meld.sort), oracle.sort_u32(k)), n
             assert np.array_equal(_sort(keys, ctx, meld.merge_sort), oracle.sort_u32(keys)), n
-        for n, by in ((1 << 13, "registers"), ((1 << 17) + 1, "radix")):
+        for n, by in ((1 << 12, "registers"), ((1 << 17) + 1, "radix")):
             assert meld.sort_plan(n, variant="auto", ctx=ctx)["sorts_by"] == by
     finally:
         meld.destroy_context(ctx)
