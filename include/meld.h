@@ -131,12 +131,13 @@ const char *meld_last_error(void);
  * the padding (0xFFFFFFFF, for pairs (0xFFFFFFFF, 0xFFFFFFFF)) never leaves
  * the positions n..N-1, takes no memory and no work, and nothing past n is
  * read or written in the caller's arrays.
- * MELD_AUTO runs the network up to 5 2^14 pairs, with MELD_OPT_SORT_LOG_TILE or
- * MELD_OPT_LANE_EXCHANGE set, and above 2^14 keys or 5 2^14 pairs under capture
- * or where the scratch below cannot be allocated. Otherwise it takes another
- * sort, which gives the same (unique) result: one workgroup in registers up to
- * 2^12 keys (2^14 without scratch), sorted runs and ranks up to 2^17 keys, and
- * above a least-significant-digit radix sort in at most four passes per word.
+ * MELD_AUTO runs the network with MELD_OPT_SORT_LOG_TILE or
+ * MELD_OPT_LANE_EXCHANGE set, for 2^16 + 1 .. 5 2^14 pairs, and above 2^14 keys
+ * or 2^12 pairs under capture or where the scratch below cannot be allocated.
+ * Otherwise it takes another sort, which gives the same (unique) result: one
+ * workgroup in registers up to 2^12 keys or 2^11 pairs (2^14 and 2^12 without
+ * scratch), sorted runs and ranks up to 2^17 keys or 2^16 pairs, and above a
+ * least-significant-digit radix sort in at most four passes per word.
  * The scratch, owned by the context, is as large as the arrays plus at most 1/8
  * of that for digit counts (9 2^14 words for the ranks).
  *

@@ -157,15 +157,18 @@ hipError_t launch_bucket_sort(uint32_t *keys, uint32_t n, uint32_t log_bucket,
 
 // Sorts keys[0..n), n <= kSmallSortMax, in one workgroup with 8 or 16 keys per
 // lane (small_sort.hip). Any 4-byte alignment.
-constexpr uint32_t kSmallSortMax = 1u << 14;
-hipError_t launch_small_sort(uint32_t *keys, uint32_t n, hipStream_t stream);
+// payload: NULL, or moved along, n <= kSmallPairsMax.
+constexpr uint32_t kSmallSortMax = 1u << 14, kSmallPairsMax = 1u << 12;
+hipError_t launch_small_sort(uint32_t *keys, uint32_t *payload, uint32_t n, hipStream_t stream);
 
 // Sorts keys[0..n), n <= kRankSortMax, by runs and ranks (rank_sort.hip).
 // scratch: kRankScratchWords u32, 16-byte aligned.
 // Up to kRankSortMin keys one workgroup is faster.
 constexpr uint32_t kRankSortMin = 1u << 12, kRankSortMax = 1u << 17;
-constexpr uint32_t kRankScratchWords = kRankSortMax + kRankSortMax / 8;
-hipError_t launch_rank_sort(uint32_t *keys, uint32_t n, uint32_t *scratch, hipStream_t stream);
+constexpr uint32_t kRankPairsMin = 1u << 11, kRankPairsMax = 1u << 16;
+constexpr uint32_t kRankScratchWords = kRankSortMax + kRankSortMax / 8;  // pairs: 2^16 of twice the size
+hipError_t launch_rank_sort(uint32_t *keys, uint32_t *payload, uint32_t n, uint32_t *scratch,
+                            hipStream_t stream);
 
 hipError_t launch_fill_u32(uint32_t *p, uint32_t value, size_t count, hipStream_t stream);
 

@@ -694,8 +694,8 @@ SortPlan fixed_plan(const meld_ctx *ctx, bool pairs, size_t n, meld_variant v) {
     return SortPlan{plan_log_tile(ctx, pairs, log2_ceil(n)), m, m, plan_xch(ctx)};
 }
 
-meld_status small_sort(uint32_t *keys, size_t n, hipStream_t s) {
-    hipError_t e = meld::launch_small_sort(keys, (uint32_t)n, s);
+meld_status small_sort(uint32_t *keys, uint32_t *payload, size_t n, hipStream_t s) {
+    hipError_t e = meld::launch_small_sort(keys, payload, (uint32_t)n, s);
     return e == hipSuccess ? MELD_OK : hip_fail(e, "small sort launch");
 }
 
@@ -710,16 +710,21 @@ meld_status small_sort(uint32_t *keys, size_t n, hipStream_t s) {
 // ranks / radix: 1000 keys 8.4 / 8.2 (bound by the calls; the kernels alone 6.6 / 3.4),
 // 2^11 10.8 / 8.2, 2^12 14.8 / 8.4, 2^13 21.2 / 13.1 / 10.9, 2^14 29.3 / - / 11.2 (the
 // kernel alone of registers 21), 2^15 33 / - / 11.3 / 35, 2^16 42 / - / 14.6 / 36, 2^17
-// - / - / 23.9 / 37; pairs with their index 2^16 67 / - / - / 54,
-// 80000 84 / - / - / 54, 2^17 81 / - / - / 55; pairs with random payloads, twice the
-// passes, 2^16 67 / - / - / 75, 80000 84 / - / - / 76, 2^17 81 / - / - / 77. An option
-// that fixes how the network runs asks for the network. Ranks and radix passes not
-// under capture: the recorded launches would hold the address of scratch that a later
-// call of the context may replace, where the others have none.
+// - / - / 23.9 / 37. Pairs: 64 12.0 / 11.7, 1000 18.8 / 12.2, 2^11 21.5 / 14.8, 2^12 29 /
+// 20.8 / 17.6, 2^14 45 / - / 18.1, 2^15 54 / - / 20.0, 2^16 67 / - / 27.8 / 54 with their
+// index, 75 with random payloads (twice the passes), 80000 84 / - / - / 54 and 76, 2^17 81
+// / - / - / 55 and 77. Up to 5 2^14 pairs above the ranks the network stays, tuned.
+// An option that fixes how the network runs asks for the network. Ranks and radix
+// passes not under capture: the recorded launches would hold the address of scratch
+// that a later call of the context may replace, where the others have none.
 enum class SortBy { kNetwork, kRegisters, kRanks, kRadix };
 SortBy auto_sort_by(const meld_ctx *ctx, bool pairs, size_t n, bool scratch) {
     if (ctx->sort_log_tile != 0 || ctx->lane_exchange >= 0) return SortBy::kNetwork;
-    if (pairs) return scratch && n > ((size_t)5 << 14) ? SortBy::kRadix : SortBy::kNetwork;
+    if (pairs) {
+        if (scratch && n > meld::kRankPairsMin && n <= meld::kRankPairsMax) return SortBy::kRanks;
+        if (n <= meld::kSmallPairsMax) return SortBy::kRegisters;
+        return scratch && n > ((size_t)5 << 14) ? SortBy::kRadix : SortBy::kNetwork;
+    }
     if (scratch && n > meld::kRankSortMin)
         return n <= meld::kRankSortMax ? SortBy::kRanks : SortBy::kRadix;
     return n <= meld::kSmallSortMax ? SortBy::kRegisters : SortBy::kNetwork;
@@ -734,7 +739,7 @@ meld_status try_scratch_sort(meld_ctx *ctx, SortBy by, uint32_t *keys, uint32_t 
                                : meld::radix_scratch_words((uint32_t)n, payload != nullptr);
     *done = ensure_words(&ctx->merge_buf, &ctx->merge_words, words, "sort scratch") == MELD_OK;
     if (!*done) return MELD_OK;
-    hipError_t e = ranks ? meld::launch_rank_sort(keys, (uint32_t)n, ctx->merge_buf, s)
+    hipError_t e = ranks ? meld::launch_rank_sort(keys, payload, (uint32_t)n, ctx->merge_buf, s)
                          : meld::launch_radix_sort(keys, payload, (uint32_t)n, ctx->merge_buf, s);
     return e == hipSuccess ? MELD_OK : hip_fail(e, ranks ? "rank sort launch" : "radix sort launch");
 }
@@ -1317,7 +1322,7 @@ meld_status meld_sort_u32(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size
             if (done) return st;
             by = auto_sort_by(ctx, pairs, n, false);
         }
-        if (by == SortBy::kRegisters) return small_sort(keys, n, s);
+        if (by == SortBy::kRegisters) return small_sort(keys, payload, n, s);
     }
     SortPlan plan = fixed_plan(ctx, payload != nullptr, n, variant);
     if (variant == MELD_AUTO) {
@@ -1522,7 +1527,7 @@ meld_status meld_merge_sort_u32(meld_ctx *ctx, uint32_t *keys, size_t n, int64_t
                                  keys, nullptr, n, s, &done);
             if (done) return st;
         }
-        if (n <= meld::kSmallSortMax) return small_sort(keys, n, s);
+        if (n <= meld::kSmallSortMax) return small_sort(keys, nullptr, n, s);
     }
     bool melded = use_melded(variant);
     if (variant == MELD_AUTO) {

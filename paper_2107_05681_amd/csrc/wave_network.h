@@ -59,21 +59,21 @@ __device__ __forceinline__ uint32_t median(uint32_t x, uint32_t y, uint32_t z) {
     return mn > t ? mn : t;
 }
 
-// Register steps on bit Q.
-template <int Q, int E>
-__device__ __forceinline__ void wave_reg_step(uint32_t (&e)[E]) {
+// Register steps on bit Q. T: u32 keys, or u64 (key, payload) composites.
+template <int Q, typename T, int E>
+__device__ __forceinline__ void wave_reg_step(T (&e)[E]) {
 #pragma unroll
     for (int r = 0; r < E; ++r)
         if ((r & (1 << Q)) == 0) {
-            const uint32_t x = e[r], y = e[r | (1 << Q)];
+            const T x = e[r], y = e[r | (1 << Q)];
             e[r] = x < y ? x : y;
             e[r | (1 << Q)] = x < y ? y : x;
         }
 }
 
 // Steps on register bits TOP .. 0.
-template <int TOP, int E>
-__device__ __forceinline__ void wave_reg_steps(uint32_t (&e)[E]) {
+template <int TOP, typename T, int E>
+__device__ __forceinline__ void wave_reg_steps(T (&e)[E]) {
     if constexpr (TOP >= 0) {
         wave_reg_step<TOP>(e);
         wave_reg_steps<TOP - 1>(e);
@@ -82,14 +82,14 @@ __device__ __forceinline__ void wave_reg_steps(uint32_t (&e)[E]) {
 
 // Phases 2^1 .. 2^(B-1), B register bits: bit M of the register index is the
 // direction.
-template <int M, int Q, int E>
-__device__ __forceinline__ void wave_first_phases(uint32_t (&e)[E]) {
+template <int M, int Q, typename T, int E>
+__device__ __forceinline__ void wave_first_phases(T (&e)[E]) {
     if constexpr (M < wave_bits<E>()) {
 #pragma unroll
         for (int r = 0; r < E; ++r)
             if ((r & (1 << Q)) == 0) {
-                const uint32_t x = e[r], y = e[r | (1 << Q)];
-                const uint32_t mn = x < y ? x : y, mx = x < y ? y : x;
+                const T x = e[r], y = e[r | (1 << Q)];
+                const T mn = x < y ? x : y, mx = x < y ? y : x;
                 e[r] = (r >> M) & 1 ? mx : mn;
                 e[r | (1 << Q)] = (r >> M) & 1 ? mn : mx;
             }
@@ -110,6 +110,18 @@ __device__ __forceinline__ void wave_lane_step(uint32_t (&e)[E], uint32_t keep) 
                       keep);
 }
 
+template <int B, int E>
+__device__ __forceinline__ void wave_lane_step(uint64_t (&e)[E], uint32_t keep) {
+    constexpr int ctrl = B == 0 ? 0xB1 : B == 1 ? 0x4E : B == 2 ? 0x141 : 0x128;
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)e[r], ctrl, 0xF, 0xF, true);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(e[r] >> 32), ctrl, 0xF, 0xF, true);
+        const uint64_t y = (uint64_t)hi << 32 | lo;
+        e[r] = (y < e[r]) != (keep != 0) ? y : e[r];
+    }
+}
+
 // Trades lane bit 4 (SWAP32: 5) for the top register bit.
 template <bool SWAP32, int E>
 __device__ __forceinline__ void wave_trade(uint32_t (&e)[E]) {
@@ -127,11 +139,25 @@ __device__ __forceinline__ void wave_trade(uint32_t (&e)[E]) {
     }
 }
 
+template <bool SWAP32, int E>
+__device__ __forceinline__ void wave_trade(uint64_t (&e)[E]) {
+    uint32_t lo[E], hi[E];
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+        lo[r] = (uint32_t)e[r];
+        hi[r] = (uint32_t)(e[r] >> 32);
+    }
+    wave_trade<SWAP32>(lo);
+    wave_trade<SWAP32>(hi);
+#pragma unroll
+    for (int r = 0; r < E; ++r) e[r] = (uint64_t)hi[r] << 32 | lo[r];
+}
+
 // Steps on element bits TOP .. 0 of a wave, B register bits. TOP = B + 5 takes
 // three trades for its two upper bits instead of four and leaves bits B + 4 and
 // B + 5 in each other's place: bit B + 4 is lane bit 5 then, bit B + 5 lane bit 4.
-template <int TOP, int E>
-__device__ __forceinline__ void wave_steps(uint32_t (&e)[E], const WaveLane &w) {
+template <int TOP, typename T, int E>
+__device__ __forceinline__ void wave_steps(T (&e)[E], const WaveLane &w) {
     constexpr int B = wave_bits<E>();
     static_assert(TOP <= B + 5, "above the wave");
     if constexpr (TOP == B + 5) {
@@ -154,10 +180,11 @@ __device__ __forceinline__ void wave_steps(uint32_t (&e)[E], const WaveLane &w) 
     }
 }
 
-template <int E>
-__device__ __forceinline__ void wave_flip(uint32_t (&e)[E], uint32_t mask) {
+// mask: 0 or ~0.
+template <typename T, int E>
+__device__ __forceinline__ void wave_flip(T (&e)[E], uint32_t mask) {
 #pragma unroll
-    for (int r = 0; r < E; ++r) e[r] ^= mask;
+    for (int r = 0; r < E; ++r) e[r] ^= (T)(int32_t)mask;
 }
 
 // The complement of phase 2^M of a sort whose last phase is 2^LAST: all ones
@@ -169,8 +196,8 @@ __device__ __forceinline__ uint32_t wave_down(uint32_t high) {
 }
 
 // Phases 2^M .. 2^min(LAST, B + 6) on keys already complemented for phase 2^M.
-template <int M, int LAST, int E>
-__device__ __forceinline__ void wave_phases(uint32_t (&e)[E], const WaveLane &w, uint32_t high) {
+template <int M, int LAST, typename T, int E>
+__device__ __forceinline__ void wave_phases(T (&e)[E], const WaveLane &w, uint32_t high) {
     constexpr int B = wave_bits<E>();
     wave_steps<M - 1>(e, w);
     if constexpr (M < LAST && M < B + 6) {
@@ -291,10 +318,44 @@ __device__ __forceinline__ uint32_t wave_group_row(const WaveLane &w, bool trade
     return ((threadIdx.x & ~63u) | id) * E;
 }
 
+// Sixteen bytes at a time between e[0 .. E) and memory aligned to them.
+template <typename T, int E>
+__device__ __forceinline__ void wave_store_row(T *to, const T (&e)[E]) {
+    if constexpr (sizeof(T) == 8) {
+#pragma unroll
+        for (int c = 0; c < E; c += 2)
+            *reinterpret_cast<ulonglong2 *>(to + c) = make_ulonglong2(e[c], e[c + 1]);
+    } else {
+#pragma unroll
+        for (int c = 0; c < E; c += 4)
+            *reinterpret_cast<uint4 *>(to + c) = make_uint4(e[c], e[c + 1], e[c + 2], e[c + 3]);
+    }
+}
+template <typename T, int E>
+__device__ __forceinline__ void wave_load_row(T (&e)[E], const T *from) {
+    if constexpr (sizeof(T) == 8) {
+#pragma unroll
+        for (int c = 0; c < E; c += 2) {
+            const ulonglong2 v = *reinterpret_cast<const ulonglong2 *>(from + c);
+            e[c] = v.x;
+            e[c + 1] = v.y;
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < E; c += 4) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(from + c);
+            e[c] = v.x;
+            e[c + 1] = v.y;
+            e[c + 2] = v.z;
+            e[c + 3] = v.w;
+        }
+    }
+}
+
 // Phases 2^M .. 2^LOG above a wave's on keys complemented for phase 2^(M-1): for the
 // steps across waves every lane takes one piece of each wave's keys.
-template <int M, int LOG, int E>
-__device__ __forceinline__ void wave_group_cross(uint32_t (&e)[E], uint32_t *s, const WaveLane &w,
+template <int M, int LOG, typename T, int E>
+__device__ __forceinline__ void wave_group_cross(T (&e)[E], T *s, const WaveLane &w,
                                                  uint32_t high) {
     if constexpr (M <= LOG) {
         constexpr int B = wave_bits<E>(), TOP = B + 5;
@@ -302,13 +363,10 @@ __device__ __forceinline__ void wave_group_cross(uint32_t (&e)[E], uint32_t *s, 
         constexpr int GB = B - WB;         // low element bits that stay registers
         static_assert(GB >= 0, "one exchange per phase");
         wave_flip(e, wave_down<M - 1, LOG, B>(high) ^ wave_down<M, LOG, B>(high));
-        uint4 *from = reinterpret_cast<uint4 *>(s + wave_phys(wave_group_row<E>(w, true)));
-#pragma unroll
-        for (int c = 0; c < E / 4; ++c)
-            from[c] = make_uint4(e[4 * c], e[4 * c + 1], e[4 * c + 2], e[4 * c + 3]);
+        wave_store_row(s + wave_phys(wave_group_row<E>(w, true)), e);
         __syncthreads();
-        uint32_t *p = s + wave_phys((uint32_t)threadIdx.x << GB);
-        auto at = [&](int r) -> uint32_t & {
+        T *p = s + wave_phys((uint32_t)threadIdx.x << GB);
+        auto at = [&](int r) -> T & {
             return p[wave_phys((uint32_t)(r >> GB) << (TOP + 1)) + (r & ((1 << GB) - 1))];
         };
 #pragma unroll
@@ -320,15 +378,7 @@ __device__ __forceinline__ void wave_group_cross(uint32_t (&e)[E], uint32_t *s, 
 #pragma unroll
         for (int r = 0; r < E; ++r) at(r) = e[r];
         __syncthreads();
-        const uint4 *to = reinterpret_cast<const uint4 *>(s + wave_phys(wave_group_row<E>(w, false)));
-#pragma unroll
-        for (int c = 0; c < E / 4; ++c) {
-            const uint4 v = to[c];
-            e[4 * c] = v.x;
-            e[4 * c + 1] = v.y;
-            e[4 * c + 2] = v.z;
-            e[4 * c + 3] = v.w;
-        }
+        wave_load_row(e, s + wave_phys(wave_group_row<E>(w, false)));
         // The next phase's writes go to the lane's own wave's keys, which only that
         // wave reads until the next barrier.
         wave_steps<TOP>(e, w);
@@ -339,8 +389,8 @@ __device__ __forceinline__ void wave_group_cross(uint32_t (&e)[E], uint32_t *s, 
 // Sorts 2^LOG keys of a workgroup from any order into rows of E per lane
 // (wave_group_row; traded for whole waves). s: 2^LOG elements of LDS
 // (wave_lds_words) where there is more than one wave.
-template <int LOG, int E>
-__device__ __forceinline__ void wave_group_sort(uint32_t (&e)[E], uint32_t *s, const WaveLane &w) {
+template <int LOG, typename T, int E>
+__device__ __forceinline__ void wave_group_sort(T (&e)[E], T *s, const WaveLane &w) {
     constexpr int B = wave_bits<E>();
     const uint32_t high = (threadIdx.x & ~63u) | w.id;
     wave_first_phases<1, 0>(e);

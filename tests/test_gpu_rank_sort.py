@@ -1,4 +1,4 @@
-"""MELD_AUTO sorts of 2^12 + 1 .. 2^17 keys (runs and ranks) against the oracle.
+"""MELD_AUTO sorts of 2^12 + 1 .. 2^17 keys and 2^11 + 1 .. 2^16 pairs (runs and ranks) against the oracle.
 
 Bar: bit-exact. Sizes at the edges of a run and of the numbers of runs the kernels are
 built for; ties within and across runs, the padding's value, sorted and reversed input;
@@ -47,5 +47,39 @@ def test_sizes_and_orders():
             assert np.array_equal(_sort(keys, ctx, meld.merge_sort), oracle.sort_u32(keys)), n
         for n, by in ((1 << 12, "registers"), ((1 << 17) + 1, "radix")):
             assert meld.sort_plan(n, variant="auto", ctx=ctx)["sorts_by"] == by
+    finally:
+        meld.destroy_context(ctx)
+
+
+def _sort_pairs(keys, vals, ctx):
+    guard = np.arange(64, dtype=np.uint32)
+    k, v = (torch.from_numpy(np.concatenate([a, guard]).view(np.int32)).to("cuda:0")
+            for a in (keys, vals))
+    meld.sort(k[:len(keys)], v[:len(keys)], variant="auto", ctx=ctx)
+    k, v = k.cpu().numpy().view(np.uint32), v.cpu().numpy().view(np.uint32)
+    assert np.array_equal(k[len(keys):], guard) and np.array_equal(v[len(keys):], guard)
+    return k[:len(keys)], v[:len(keys)]
+
+
+@pytest.mark.parametrize("log", range(1, 17))
+def test_pairs(log):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    ctx = meld.new_context(0)
+    try:
+        for n in sorted({max(2, (1 << log) - 1), 1 << log, min(1 << 16, (1 << log) + 1),
+                         3 << (log - 1)} - {3 << 15}):
+            by = meld.sort_plan(n, pairs=True, variant="auto", ctx=ctx)["sorts_by"]
+            assert by == ("registers" if n <= 1 << 11 else "ranks")
+            keys, vals = workloads.keys_u32(n, n), workloads.keys_u32(n + 1, n)
+            ends, vends = keys % np.uint32(2), vals.copy()
+            ends[::3] = vends[::3] = 0xFFFFFFFF
+            index = np.arange(n, dtype=np.uint32)
+            for k, v in ((keys, vals), (keys % np.uint32(5), index), (ends, vends),
+                         (np.sort(keys)[::-1], index[::-1]), (vals & np.uint32(1), keys)):
+                k, v = np.ascontiguousarray(k), np.ascontiguousarray(v)
+                rk, rv = oracle.sort_pairs_u32(k, v)
+                gk, gv = _sort_pairs(k, v, ctx)
+                assert np.array_equal(gk, rk) and np.array_equal(gv, rv), n
     finally:
         meld.destroy_context(ctx)

@@ -69,3 +69,21 @@ def test_captured(n):
         buf.copy_(torch.from_numpy(keys.view(np.int32)))
         graph.replay()
         assert np.array_equal(buf.cpu().numpy().view(np.uint32), oracle.sort_u32(keys))
+
+
+@pytest.mark.parametrize("n", [(1 << 11) + 1, 3000, 1 << 12])
+def test_captured_pairs(n):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    key, val = (torch.zeros(n, dtype=torch.int32, device="cuda:0") for _ in range(2))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        meld.sort(key, val, variant="auto")
+    for seed in range(3):
+        k, v = workloads.keys_u32(seed, n) % np.uint32(64), workloads.keys_u32(seed + 9, n)
+        key.copy_(torch.from_numpy(k.view(np.int32)))
+        val.copy_(torch.from_numpy(v.view(np.int32)))
+        graph.replay()
+        rk, rv = oracle.sort_pairs_u32(k, v)
+        assert np.array_equal(key.cpu().numpy().view(np.uint32), rk)
+        assert np.array_equal(val.cpu().numpy().view(np.uint32), rv)
