@@ -278,8 +278,9 @@ meld_status meld_oddeven_sort_buckets_u32(meld_ctx *ctx, uint32_t *keys, size_t 
  * once per shape class.
  *
  * keys:    device u32[n], n < 2^31.
- * Scratch: a second buffer of n keys (MELD_AUTO: at most 9/8 n), owned by the
- *          context.
+ * Scratch: a second buffer of n keys and the cuts of its tiles for the merge
+ *          passes, which a context keeps until it ends once a capture has taken
+ *          their addresses; MELD_AUTO: meld_sort_u32's.
  * Errors:  MELD_EINVAL for NULL/host pointers or n >= 2^31. */
 meld_status meld_merge_sort_u32(meld_ctx *ctx, uint32_t *keys, size_t n, int64_t max_passes,
                                 meld_variant variant, void *stream);

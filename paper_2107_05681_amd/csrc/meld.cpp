@@ -59,12 +59,20 @@ struct meld_ctx {
     // the caller's data, and device counters for the divergence probes.
     meld::Tuner tuner;
     uint32_t *tune_buf = nullptr;
-    // Merge sort: the other buffer of each merge pass.
+    size_t tune_words = 0;
+    // Scratch of the sorts by ranks and radix passes, which are never captured:
+    // nothing but the calls in flight holds its address.
+    uint32_t *sort_buf = nullptr;
+    size_t sort_words = 0;
+    // Merge sort: the other buffer of each merge pass. A captured merge sort holds
+    // the addresses of both buffers, so once a capture has taken them, outgrown
+    // ones are kept until the context ends.
     uint32_t *merge_buf = nullptr;
     size_t merge_words = 0;
     uint32_t *merge_cuts = nullptr;  // merge-path cut of every tile of a merge pass
     size_t merge_cut_words = 0;
-    size_t tune_words = 0;
+    bool merge_captured = false;
+    std::vector<uint32_t *> retired;
     unsigned long long *probe_buf = nullptr;  // kProbeWords counters
     double theta = 0.5;  // mixed-wave fraction from which the probe favours melding
     double tie = 0.02;   // trials within 2 % count as ties
@@ -737,10 +745,10 @@ meld_status try_scratch_sort(meld_ctx *ctx, SortBy by, uint32_t *keys, uint32_t 
     const bool ranks = by == SortBy::kRanks;
     const size_t words = ranks ? (size_t)meld::kRankScratchWords
                                : meld::radix_scratch_words((uint32_t)n, payload != nullptr);
-    *done = ensure_words(&ctx->merge_buf, &ctx->merge_words, words, "sort scratch") == MELD_OK;
+    *done = ensure_words(&ctx->sort_buf, &ctx->sort_words, words, "sort scratch") == MELD_OK;
     if (!*done) return MELD_OK;
-    hipError_t e = ranks ? meld::launch_rank_sort(keys, payload, (uint32_t)n, ctx->merge_buf, s)
-                         : meld::launch_radix_sort(keys, payload, (uint32_t)n, ctx->merge_buf, s);
+    hipError_t e = ranks ? meld::launch_rank_sort(keys, payload, (uint32_t)n, ctx->sort_buf, s)
+                         : meld::launch_radix_sort(keys, payload, (uint32_t)n, ctx->sort_buf, s);
     return e == hipSuccess ? MELD_OK : hip_fail(e, ranks ? "rank sort launch" : "radix sort launch");
 }
 
@@ -1155,16 +1163,30 @@ meld_status auto_two_forms(meld_ctx *ctx, const char *op, const std::string &key
 // context's merge buffer; the result ends in keys.
 constexpr uint32_t kMergeRunLog = 10;
 
+// The buffers of a merge sort of n keys.
+meld_status ensure_merge(meld_ctx *ctx, size_t n) {
+    const size_t cuts = meld::merge_pass_cut_words((uint32_t)n);
+    if (ctx->merge_captured && (n > ctx->merge_words || cuts > ctx->merge_cut_words)) {
+        for (uint32_t **p : {&ctx->merge_buf, &ctx->merge_cuts}) {
+            if (*p != nullptr) ctx->retired.push_back(*p);
+            *p = nullptr;
+        }
+        ctx->merge_words = ctx->merge_cut_words = 0;
+        ctx->merge_captured = false;
+    }
+    meld_status st = ensure_words(&ctx->merge_buf, &ctx->merge_words, n, "merge buffer");
+    if (st != MELD_OK) return st;
+    return ensure_words(&ctx->merge_cuts, &ctx->merge_cut_words, cuts, "merge cuts");
+}
+
 meld_status merge_sort_impl(meld_ctx *ctx, uint32_t *keys, size_t n, int64_t max_passes,
                             bool melded, hipStream_t s) {
     hipError_t e = meld::launch_oddeven_buckets(keys, (uint32_t)n, kMergeRunLog, -1, melded, s);
     if (e != hipSuccess) return hip_fail(e, "odd-even launch");
     if (n <= (1u << kMergeRunLog) || max_passes == 0) return MELD_OK;
-    meld_status st = ensure_words(&ctx->merge_buf, &ctx->merge_words, n, "merge buffer");
+    meld_status st = ensure_merge(ctx, n);
     if (st != MELD_OK) return st;
-    st = ensure_words(&ctx->merge_cuts, &ctx->merge_cut_words,
-                      meld::merge_pass_cut_words((uint32_t)n), "merge cuts");
-    if (st != MELD_OK) return st;
+    if (capturing(s)) ctx->merge_captured = true;
     uint32_t *src = keys, *dst = ctx->merge_buf;
     int64_t pass = 0;
     for (uint32_t lr = kMergeRunLog; ((size_t)1 << lr) < n; ++lr) {
@@ -1291,9 +1313,10 @@ void meld_destroy(meld_ctx *ctx) {
     if (ctx->capture_stream != nullptr) (void)hipStreamDestroy(ctx->capture_stream);
     for (void *p : {(void *)ctx->seg_state, (void *)ctx->seg_cls,
                     (void *)ctx->seg_queue, (void *)ctx->seg_work, (void *)ctx->tune_buf,
-                    (void *)ctx->merge_buf, (void *)ctx->merge_cuts, (void *)ctx->probe_buf,
-                    (void *)ctx->seg_auto})
+                    (void *)ctx->sort_buf, (void *)ctx->merge_buf, (void *)ctx->merge_cuts,
+                    (void *)ctx->probe_buf, (void *)ctx->seg_auto})
         if (p != nullptr) (void)hipFree(p);
+    for (uint32_t *p : ctx->retired) (void)hipFree(p);
     if (ctx->seg_total != nullptr) (void)hipHostFree(ctx->seg_total);
     if (ctx->seg_total_ready != nullptr) (void)hipEventDestroy(ctx->seg_total_ready);
     delete ctx;
