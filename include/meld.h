@@ -273,14 +273,16 @@ meld_status meld_oddeven_sort_buckets_u32(meld_ctx *ctx, uint32_t *keys, size_t 
  * sides (emit, advance, load the next key of that run) as written, the melded
  * form selects the emitted key and issues one load from a selected address.
  * Ties take run A first. MELD_AUTO with all passes sorts as meld_sort_u32 does
- * (in registers, by ranks or by radix passes); with max_passes, and above 2^14
- * keys under capture or without the memory for the scratch, it times both forms
- * once per shape class.
+ * (in registers, by ranks or by radix passes). With max_passes, and without the
+ * memory for the scratch, it times both forms once per shape class. Above 2^14
+ * keys under capture it runs the form that the tuner holds, else the melded one.
+ * A capture cannot allocate: a call outside one, of as many keys or more, in any
+ * form or MELD_AUTO, has to come before a captured one that merges.
  *
  * keys:    device u32[n], n < 2^31.
  * Scratch: a second buffer of n keys and the cuts of its tiles for the merge
  *          passes, which a context keeps until it ends once a capture has taken
- *          their addresses; MELD_AUTO: meld_sort_u32's.
+ *          their addresses; MELD_AUTO: meld_sort_u32's too.
  * Errors:  MELD_EINVAL for NULL/host pointers or n >= 2^31. */
 meld_status meld_merge_sort_u32(meld_ctx *ctx, uint32_t *keys, size_t n, int64_t max_passes,
                                 meld_variant variant, void *stream);

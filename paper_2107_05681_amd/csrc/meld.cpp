@@ -1541,9 +1541,13 @@ meld_status meld_merge_sort_u32(meld_ctx *ctx, uint32_t *keys, size_t n, int64_t
     // All passes: only the sorted array counts (with the copy of the input, against
     // the faster form of the merge sort, microseconds: 1000 keys 8.2 / 17.6, 2^14
     // 11.2 / 47.5, 2^15 11.3 / 62, 2^20 55 / 135, 2^24 228 / 696). Above 2^14 keys under
-    // capture, and without the memory for the scratch, the merge passes.
+    // capture, and without the memory for the scratch, the merge passes. A capture
+    // cannot allocate, so a call outside one sees to the merge buffers too: it is the
+    // warm-up of a later capture of n keys, whichever form that asks for.
     if (variant == MELD_AUTO && max_passes < 0) {
-        if (n > meld::kRankSortMin && !capturing(s)) {
+        const bool eager = !capturing(s);
+        if (eager && n > (1u << kMergeRunLog)) (void)ensure_merge(ctx, n);
+        if (eager && n > meld::kRankSortMin) {
             bool done = false;
             meld_status st =
                 try_scratch_sort(ctx, n <= meld::kRankSortMax ? SortBy::kRanks : SortBy::kRadix,

@@ -66,3 +66,16 @@ def test_later_calls_leave_a_captured_merge_sort_its_buffers(ctx, variant):
         _replay(graph, work, workloads.keys_u32(3, n), 2)
         assert np.array_equal(kd.cpu().numpy().view(np.uint32), oracle.sort_u32(other))
         assert bool((junk == -1).all())
+
+
+@pytest.mark.parametrize("variant", ["auto", "melded", "divergent"])
+@pytest.mark.parametrize("n", [5000, (1 << 14) + 1, 70_001, 1 << 18])
+def test_an_eager_auto_call_is_the_warm_up_of_a_capture(ctx, n, variant):
+    keys = workloads.keys_u32(4, n)
+    work = _to_dev(keys)
+    meld.merge_sort(work, variant="auto", ctx=ctx)
+    torch.cuda.synchronize()
+    assert np.array_equal(work.cpu().numpy().view(np.uint32), oracle.sort_u32(keys))
+    graph = _capture(ctx, work, variant)
+    for seed in (4, 5, 6):
+        _replay(graph, work, workloads.keys_u32(seed, n))
