@@ -40,11 +40,11 @@
  *     MELD_EINVAL with a message in meld_last_error(); the arrays are then
  *     untouched. A failed launch returns MELD_EHIP.
  *   - A context's scratch (segmented-sort queues, radix, merge and tuning
- *     buffers) is shared by every call on it. Calls on one context must not
- *     overlap from several host threads, and must all be enqueued on one
- *     stream (or on streams ordered by events): two calls on one context on
- *     streams that run concurrently race on that scratch. Use one context per
- *     stream.
+ *     buffers) is shared by every call on it. A call holds the context's lock
+ *     until it returns, so calls from several host threads take turns, but all
+ *     of them must be enqueued on one stream (or on streams ordered by events):
+ *     two calls on one context on streams that run concurrently race on that
+ *     scratch. Use one context per stream.
  *   - The library never calls exit() or abort().
  */
 #ifndef MELD_H

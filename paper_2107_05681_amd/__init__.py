@@ -62,7 +62,8 @@ _lib = None
 _lock = threading.Lock()
 # One library context per (device, stream): a context's scratch (segmented-sort
 # queues, radix, merge and tuning buffers) is shared by every call on
-# it, so calls on streams that may run concurrently must not share one.
+# it, so calls on streams that may run concurrently must not share one. Threads
+# that use one stream do: the library lets their calls take turns.
 _ctxs: dict[tuple[int, int], ctypes.c_void_p] = {}
 _options: dict[int, dict[int, int]] = {}  # device -> option -> value, for every context
 

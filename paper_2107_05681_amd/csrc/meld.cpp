@@ -19,6 +19,9 @@
 using meld::SortArray;
 
 struct meld_ctx {
+    // Held by every call on the context, so that the launches of two host threads'
+    // calls, which share the scratch below, go to the stream one call after the other.
+    std::mutex mu;
     int device = 0;
     // Segmented sort: queue state, per-segment class and queue, and the
     // per-workgroup padding scratch of the persistent grid.
@@ -1222,6 +1225,7 @@ meld_status region_entry(meld_ctx *ctx, const float *x, float *y, size_t n, cons
     if ((unsigned)variant > MELD_MELDED_INPLACE)
         return fail(MELD_EINVAL, "%s: bad variant", name);
     if (n == 0) return MELD_OK;
+    std::lock_guard<std::mutex> lock(ctx->mu);
     DeviceGuard g(ctx->device);
     if (!is_device_ptr(ctx, x) || !is_device_ptr(ctx, y) || !is_device_ptr(ctx, tab))
         return fail(MELD_EINVAL,
@@ -1328,6 +1332,7 @@ meld_status meld_sort_u32(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size
     if (n >= (1ull << 31)) return fail(MELD_EINVAL, "meld_sort_u32: n = %zu >= 2^31", n);
     if ((unsigned)variant > MELD_MELDED_INPLACE) return fail(MELD_EINVAL, "meld_sort_u32: bad variant");
     if (n <= 1) return MELD_OK;
+    std::lock_guard<std::mutex> lock(ctx->mu);
     DeviceGuard g(ctx->device);
     if (!is_device_ptr(ctx, keys))
         return fail(MELD_EINVAL, "meld_sort_u32: keys is not a device pointer on device %d",
@@ -1362,6 +1367,7 @@ meld_status meld_sort_u32_noalloc(meld_ctx *ctx, uint32_t *keys, uint32_t *paylo
     if (n >= (1ull << 31)) return fail(MELD_EINVAL, "%s: n = %zu >= 2^31", name, n);
     if ((unsigned)variant > MELD_MELDED_INPLACE) return fail(MELD_EINVAL, "%s: bad variant", name);
     if (n <= 1) return MELD_OK;
+    std::lock_guard<std::mutex> lock(ctx->mu);
     DeviceGuard g(ctx->device);
     if (!is_device_ptr(ctx, keys) || (payload != nullptr && !is_device_ptr(ctx, payload)))
         return fail(MELD_EINVAL, "%s: keys and payload must be device pointers on device %d",
@@ -1394,6 +1400,7 @@ meld_status meld_sort_u32_timed(meld_ctx *ctx, uint32_t *keys, uint32_t *payload
     if (n >= (1ull << 31)) return fail(MELD_EINVAL, "%s: n = %zu >= 2^31", name, n);
     if ((unsigned)variant > MELD_MELDED_INPLACE) return fail(MELD_EINVAL, "%s: bad variant", name);
     if (n <= 1) return MELD_OK;
+    std::lock_guard<std::mutex> lock(ctx->mu);
     DeviceGuard g(ctx->device);
     if (!is_device_ptr(ctx, keys) || (payload != nullptr && !is_device_ptr(ctx, payload)))
         return fail(MELD_EINVAL, "%s: keys and payload must be device pointers on device %d",
@@ -1447,6 +1454,7 @@ meld_status meld_sort_plan_describe(meld_ctx *ctx, size_t n, int with_payload,
     bool tuned = false;
     const char *by = "network";
     if (ctx != nullptr) {
+        std::lock_guard<std::mutex> lock(ctx->mu);
         if (variant == MELD_AUTO) {
             constexpr const char *kNames[] = {"network", "registers", "ranks", "radix"};
             by = kNames[(int)auto_sort_by(ctx, pairs, n, true)];
@@ -1497,6 +1505,7 @@ meld_status meld_oddeven_sort_buckets_u32(meld_ctx *ctx, uint32_t *keys, size_t 
         return fail(MELD_EINVAL, "%s: log_bucket = %u outside 6..14", name, log_bucket);
     if ((unsigned)variant > MELD_MELDED_INPLACE) return fail(MELD_EINVAL, "%s: bad variant", name);
     if (n == 0 || max_steps == 0) return MELD_OK;
+    std::lock_guard<std::mutex> lock(ctx->mu);
     DeviceGuard g(ctx->device);
     if (!is_device_ptr(ctx, keys))
         return fail(MELD_EINVAL, "%s: keys is not a device pointer on device %d", name,
@@ -1533,6 +1542,7 @@ meld_status meld_merge_sort_u32(meld_ctx *ctx, uint32_t *keys, size_t n, int64_t
     if (n >= (1ull << 31)) return fail(MELD_EINVAL, "%s: n = %zu >= 2^31", name, n);
     if ((unsigned)variant > MELD_MELDED_INPLACE) return fail(MELD_EINVAL, "%s: bad variant", name);
     if (n <= 1) return MELD_OK;
+    std::lock_guard<std::mutex> lock(ctx->mu);
     DeviceGuard g(ctx->device);
     if (!is_device_ptr(ctx, keys))
         return fail(MELD_EINVAL, "%s: keys is not a device pointer on device %d", name,
@@ -1573,6 +1583,7 @@ meld_status meld_sort_u32_steps(meld_ctx *ctx, uint32_t *keys, uint32_t *payload
         return fail(MELD_EINVAL, "meld_sort_u32_steps: n = %zu is not a power of two in [2, 2^30]",
                     n);
     if ((unsigned)variant > MELD_MELDED_INPLACE) return fail(MELD_EINVAL, "meld_sort_u32_steps: bad variant");
+    std::lock_guard<std::mutex> lock(ctx->mu);
     DeviceGuard g(ctx->device);
     if (!is_device_ptr(ctx, keys) || (payload != nullptr && !is_device_ptr(ctx, payload)))
         return fail(MELD_EINVAL, "meld_sort_u32_steps: arrays must be device pointers");
@@ -1609,6 +1620,7 @@ meld_status meld_region3_f32(meld_ctx *ctx, const float *x, float *y, size_t n,
     if (way0.trips > 65536 || way1.trips > 65536 || way2.trips > 65536)
         return fail(MELD_EINVAL, "%s: trips > 65536", name);
     if (n == 0) return MELD_OK;
+    std::lock_guard<std::mutex> lock(ctx->mu);
     DeviceGuard g(ctx->device);
     st = check_region_pointers(name, ctx, x, y, tab);
     if (st != MELD_OK) return st;
@@ -1653,6 +1665,7 @@ meld_status meld_region_lanetrips_f32(meld_ctx *ctx, const float *x, float *y, s
         if (r->trips_hi > 65536) return fail(MELD_EINVAL, "%s: trips > 65536", name);
     }
     if (n == 0) return MELD_OK;
+    std::lock_guard<std::mutex> lock(ctx->mu);
     DeviceGuard g(ctx->device);
     st = check_region_pointers(name, ctx, x, y, tab);
     if (st != MELD_OK) return st;
@@ -1689,6 +1702,7 @@ meld_status meld_segmented_sort_u32(meld_ctx *ctx, uint32_t *keys, size_t n_keys
     if (ctx == nullptr) return fail(MELD_EINVAL, "meld_segmented_sort_u32: ctx is NULL");
     if ((unsigned)variant > MELD_MELDED_INPLACE)
         return fail(MELD_EINVAL, "meld_segmented_sort_u32: bad variant");
+    std::lock_guard<std::mutex> lock(ctx->mu);
     const hipStream_t s = static_cast<hipStream_t>(stream);
     bool lo = use_melded(variant), hi = lo, xch = plan_xch(ctx);
     if (variant == MELD_AUTO && nseg > 0 && nseg < (1ull << 31)) {
@@ -1722,6 +1736,7 @@ meld_status meld_segmented_sort_u32_staged(meld_ctx *ctx, uint32_t *keys, size_t
     if (ctx == nullptr) return fail(MELD_EINVAL, "meld_segmented_sort_u32_staged: ctx is NULL");
     if ((unsigned)low_phases > MELD_MELDED_INPLACE || (unsigned)high_phases > MELD_MELDED_INPLACE)
         return fail(MELD_EINVAL, "meld_segmented_sort_u32_staged: bad variant");
+    std::lock_guard<std::mutex> lock(ctx->mu);
     return segmented_impl(ctx, keys, n_keys, offsets, nseg, use_melded(low_phases),
                           use_melded(high_phases), plan_xch(ctx), static_cast<hipStream_t>(stream),
                           "meld_segmented_sort_u32_staged");
@@ -1730,6 +1745,7 @@ meld_status meld_segmented_sort_u32_staged(meld_ctx *ctx, uint32_t *keys, size_t
 meld_status meld_tune(meld_ctx *ctx, const char *cache_path) {
     if (ctx == nullptr || cache_path == nullptr)
         return fail(MELD_EINVAL, "meld_tune: ctx and cache_path must not be NULL");
+    std::lock_guard<std::mutex> lock(ctx->mu);
     if (!ctx->tuner.attach(cache_path))
         return fail(MELD_EINVAL, "meld_tune: malformed tuning cache %s", cache_path);
     return MELD_OK;
@@ -1738,6 +1754,7 @@ meld_status meld_tune(meld_ctx *ctx, const char *cache_path) {
 meld_status meld_plan_describe(meld_ctx *ctx, char *buf, size_t len) {
     if (ctx == nullptr || buf == nullptr)
         return fail(MELD_EINVAL, "meld_plan_describe: ctx and buf must not be NULL");
+    std::lock_guard<std::mutex> lock(ctx->mu);
     const std::string d = ctx->tuner.describe();
     if (d.size() + 1 > len)
         return fail(MELD_EINVAL, "meld_plan_describe: buffer too small (need %zu bytes)",
@@ -1758,6 +1775,7 @@ meld_status meld_probe_region(meld_ctx *ctx, size_t n, uint64_t seed, uint64_t t
         return fail(MELD_EINVAL, "meld_probe_region: ctx and out must not be NULL");
     if (n >= (1ull << 32) || thr > (1ull << 32))
         return fail(MELD_EINVAL, "meld_probe_region: n >= 2^32 or thr > 2^32");
+    std::lock_guard<std::mutex> lock(ctx->mu);
     DeviceGuard g(ctx->device);
     unsigned long long c[3] = {0, 0, 0};
     const hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1772,6 +1790,7 @@ meld_status meld_probe_network(meld_ctx *ctx, uint32_t log_t, uint64_t *out, voi
     if (ctx == nullptr || out == nullptr)
         return fail(MELD_EINVAL, "meld_probe_network: ctx and out must not be NULL");
     if (log_t < 1 || log_t > 16) return fail(MELD_EINVAL, "meld_probe_network: log_t not in 1..16");
+    std::lock_guard<std::mutex> lock(ctx->mu);
     DeviceGuard g(ctx->device);
     unsigned long long c[32] = {0};
     const hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1789,6 +1808,7 @@ meld_status meld_probe_segments(meld_ctx *ctx, const uint32_t *offsets, size_t n
     if (nseg >= (1ull << 31)) return fail(MELD_EINVAL, "meld_probe_segments: nseg >= 2^31");
     for (int i = 0; i < 4; ++i) out[i] = 0;
     if (nseg == 0) return MELD_OK;
+    std::lock_guard<std::mutex> lock(ctx->mu);
     DeviceGuard g(ctx->device);
     if (!is_device_ptr(ctx, offsets))
         return fail(MELD_EINVAL, "meld_probe_segments: offsets must be a device pointer");
@@ -1803,6 +1823,7 @@ meld_status meld_probe_segments(meld_ctx *ctx, const uint32_t *offsets, size_t n
 
 meld_status meld_set_option(meld_ctx *ctx, meld_option option, int64_t value) {
     if (ctx == nullptr) return fail(MELD_EINVAL, "meld_set_option: ctx is NULL");
+    std::lock_guard<std::mutex> lock(ctx->mu);
     switch (option) {
         case MELD_OPT_USE_GRAPHS:
             ctx->use_graphs = value != 0;
@@ -1826,6 +1847,7 @@ meld_status meld_set_option(meld_ctx *ctx, meld_option option, int64_t value) {
 
 meld_status meld_segmented_sort_check(meld_ctx *ctx, void *stream) {
     if (ctx == nullptr) return fail(MELD_EINVAL, "meld_segmented_sort_check: ctx is NULL");
+    std::lock_guard<std::mutex> lock(ctx->mu);
     if (ctx->seg_state == nullptr) return MELD_OK;
     DeviceGuard g(ctx->device);
     hipError_t e = hipStreamSynchronize(static_cast<hipStream_t>(stream));
