@@ -138,8 +138,11 @@ const char *meld_last_error(void);
  * workgroup in registers up to 2^12 keys or 2^11 pairs (2^14 and 2^12 without
  * scratch), sorted runs and ranks up to 2^17 keys or 2^16 pairs, and above a
  * least-significant-digit radix sort in at most four passes per word.
- * The scratch, owned by the context, is as large as the arrays plus at most 1/8
- * of that for digit counts (9 2^14 words for the ranks).
+ * The scratch, owned by the context, is 9 2^14 words for the ranks, and for the radix
+ * sort a second copy of the arrays and 256 counts per tile of 2^11 to 2^13 elements
+ * (the tiles rounded up to a multiple of 16), with small tables. It is sized for the
+ * next power of two of n, so that it grows once per power of two, or for n itself
+ * where that much memory is not there.
  *
  * keys:    device u32[n], sorted in place (unsigned order).
  * payload: NULL, or device u32[n] moved with its key. With a payload the
@@ -281,8 +284,9 @@ meld_status meld_oddeven_sort_buckets_u32(meld_ctx *ctx, uint32_t *keys, size_t 
  *
  * keys:    device u32[n], n < 2^31.
  * Scratch: a second buffer of n keys and the cuts of its tiles for the merge
- *          passes, which a context keeps until it ends once a capture has taken
- *          their addresses; MELD_AUTO: meld_sort_u32's too.
+ *          passes, sized as meld_sort_u32's, which a context keeps until it ends
+ *          once a capture has taken their addresses; MELD_AUTO: meld_sort_u32's
+ *          too.
  * Errors:  MELD_EINVAL for NULL/host pointers or n >= 2^31. */
 meld_status meld_merge_sort_u32(meld_ctx *ctx, uint32_t *keys, size_t n, int64_t max_passes,
                                 meld_variant variant, void *stream);

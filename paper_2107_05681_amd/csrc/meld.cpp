@@ -741,14 +741,29 @@ SortBy auto_sort_by(const meld_ctx *ctx, bool pairs, size_t n, bool scratch) {
     return n <= meld::kSmallSortMax ? SortBy::kRegisters : SortBy::kNetwork;
 }
 
+// Grows a buffer to the words that words_of(n) asks for, and then at once to those of
+// the next power of two, so that calls of slowly growing n do not each wait for the
+// device and allocate; to no more than n's where the memory is not there.
+template <class WordsOf>
+meld_status ensure_class(uint32_t **buf, size_t *have, size_t n, WordsOf words_of,
+                         const char *what) {
+    const size_t need = words_of(n);
+    if (need <= *have) return MELD_OK;
+    const size_t room = std::max<size_t>(need, words_of((size_t)1 << log2_ceil(n)));
+    if (ensure_words(buf, have, room, what) == MELD_OK) return MELD_OK;
+    return ensure_words(buf, have, need, what);
+}
+
 // A sort by ranks or radix passes on the context's scratch; *done is false where
 // that cannot be allocated.
 meld_status try_scratch_sort(meld_ctx *ctx, SortBy by, uint32_t *keys, uint32_t *payload, size_t n,
                              hipStream_t s, bool *done) {
     const bool ranks = by == SortBy::kRanks;
-    const size_t words = ranks ? (size_t)meld::kRankScratchWords
-                               : meld::radix_scratch_words((uint32_t)n, payload != nullptr);
-    *done = ensure_words(&ctx->sort_buf, &ctx->sort_words, words, "sort scratch") == MELD_OK;
+    auto words = [&](size_t m) {
+        return ranks ? (size_t)meld::kRankScratchWords
+                     : meld::radix_scratch_words((uint32_t)m, payload != nullptr);
+    };
+    *done = ensure_class(&ctx->sort_buf, &ctx->sort_words, n, words, "sort scratch") == MELD_OK;
     if (!*done) return MELD_OK;
     hipError_t e = ranks ? meld::launch_rank_sort(keys, payload, (uint32_t)n, ctx->sort_buf, s)
                          : meld::launch_radix_sort(keys, payload, (uint32_t)n, ctx->sort_buf, s);
@@ -1168,8 +1183,8 @@ constexpr uint32_t kMergeRunLog = 10;
 
 // The buffers of a merge sort of n keys.
 meld_status ensure_merge(meld_ctx *ctx, size_t n) {
-    const size_t cuts = meld::merge_pass_cut_words((uint32_t)n);
-    if (ctx->merge_captured && (n > ctx->merge_words || cuts > ctx->merge_cut_words)) {
+    auto cuts = [](size_t m) { return meld::merge_pass_cut_words((uint32_t)m); };
+    if (ctx->merge_captured && (n > ctx->merge_words || cuts(n) > ctx->merge_cut_words)) {
         for (uint32_t **p : {&ctx->merge_buf, &ctx->merge_cuts}) {
             if (*p != nullptr) ctx->retired.push_back(*p);
             *p = nullptr;
@@ -1177,9 +1192,10 @@ meld_status ensure_merge(meld_ctx *ctx, size_t n) {
         ctx->merge_words = ctx->merge_cut_words = 0;
         ctx->merge_captured = false;
     }
-    meld_status st = ensure_words(&ctx->merge_buf, &ctx->merge_words, n, "merge buffer");
+    meld_status st = ensure_class(
+        &ctx->merge_buf, &ctx->merge_words, n, [](size_t m) { return m; }, "merge buffer");
     if (st != MELD_OK) return st;
-    return ensure_words(&ctx->merge_cuts, &ctx->merge_cut_words, cuts, "merge cuts");
+    return ensure_class(&ctx->merge_cuts, &ctx->merge_cut_words, n, cuts, "merge cuts");
 }
 
 meld_status merge_sort_impl(meld_ctx *ctx, uint32_t *keys, size_t n, int64_t max_passes,
