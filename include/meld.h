@@ -233,7 +233,8 @@ meld_status meld_sort_plan_describe(meld_ctx *ctx, size_t n, int with_payload,
  * ascending order in registers, which gives the same (unique) result, and runs
  * the faster. Scratch: 5 bytes per segment plus 256 KiB per resident workgroup
  * (one per CU) for staging segments of more than 2^14 keys, owned by the
- * context.
+ * context, which keeps outgrown queues until it ends once a capture has taken
+ * their addresses.
  * Errors:  MELD_EINVAL for NULL/host pointers. Offsets live on the device
  *          and are not inspected on the host: a segment longer than 65536,
  *          decreasing offsets, offsets[0] != 0 or an offset above n_keys

@@ -29,6 +29,9 @@ struct meld_ctx {
     uint8_t *seg_cls = nullptr;
     uint32_t *seg_queue = nullptr;
     size_t seg_cap = 0;  // segments the two arrays above hold
+    // A capture of the caller's holds their addresses: outgrown ones are kept until
+    // the context ends.
+    bool seg_captured = false;
     uint32_t *seg_work = nullptr;
     uint32_t seg_grid = 0;
     // The segmented sort in registers: its states (two, used in turn), host memory
@@ -75,7 +78,7 @@ struct meld_ctx {
     uint32_t *merge_cuts = nullptr;  // merge-path cut of every tile of a merge pass
     size_t merge_cut_words = 0;
     bool merge_captured = false;
-    std::vector<uint32_t *> retired;
+    std::vector<void *> retired;
     unsigned long long *probe_buf = nullptr;  // kProbeWords counters
     double theta = 0.5;  // mixed-wave fraction from which the probe favours melding
     double tie = 0.02;   // trials within 2 % count as ties
@@ -267,8 +270,13 @@ meld_status ensure_seg(meld_ctx *ctx, size_t nseg) {
             // Every captured graph holds the old arrays' addresses: none may
             // be replayed after they are freed, whichever caller grows them.
             drop_seg_graphs(ctx);
-            (void)hipFree(ctx->seg_cls);
-            (void)hipFree(ctx->seg_queue);
+            for (void *p : {(void *)ctx->seg_cls, (void *)ctx->seg_queue}) {
+                if (ctx->seg_captured)
+                    ctx->retired.push_back(p);
+                else
+                    (void)hipFree(p);
+            }
+            ctx->seg_captured = false;
             ctx->seg_cls = nullptr;
             ctx->seg_queue = nullptr;
             ctx->seg_cap = 0;
@@ -399,6 +407,7 @@ meld_status segmented_impl(meld_ctx *ctx, uint32_t *keys, size_t n_keys, const u
     hipError_t e = hipStreamIsCapturing(stream, &cs);
     if (e != hipSuccess) return hip_fail(e, "hipStreamIsCapturing");
     if (!ctx->use_graphs || cs != hipStreamCaptureStatusNone) {
+        if (cs != hipStreamCaptureStatusNone) ctx->seg_captured = true;
         e = meld::launch_segmented_sort(keys, key_bound(n_keys), offsets, (uint32_t)nseg,
                                         ctx->seg_state, ctx->seg_cls, ctx->seg_queue,
                                         ctx->seg_work, ctx->seg_grid, meld_lo, meld_hi, xch,
@@ -1336,7 +1345,8 @@ void meld_destroy(meld_ctx *ctx) {
                     (void *)ctx->sort_buf, (void *)ctx->merge_buf, (void *)ctx->merge_cuts,
                     (void *)ctx->probe_buf, (void *)ctx->seg_auto})
         if (p != nullptr) (void)hipFree(p);
-    for (uint32_t *p : ctx->retired) (void)hipFree(p);
+    for (void *p : ctx->retired)
+        if (p != nullptr) (void)hipFree(p);
     if (ctx->seg_total != nullptr) (void)hipHostFree(ctx->seg_total);
     if (ctx->seg_total_ready != nullptr) (void)hipEventDestroy(ctx->seg_total_ready);
     delete ctx;

@@ -1,7 +1,9 @@
-"""Captured merge sorts: their graphs stay valid whatever the context runs later.
+"""Captured merge and segmented sorts: their graphs stay valid whatever the context runs
+later.
 
 Bar: bit-exact against the oracle at every replay, with eager work of the same context
-(a larger sort by radix passes, a larger merge sort) and synchronisations in between.
+(a larger sort by radix passes, a larger merge sort, more segments) and synchronisations
+in between.
 """
 import numpy as np
 import pytest
@@ -79,3 +81,35 @@ def test_an_eager_auto_call_is_the_warm_up_of_a_capture(ctx, n, variant):
     graph = _capture(ctx, work, variant)
     for seed in (4, 5, 6):
         _replay(graph, work, workloads.keys_u32(seed, n))
+
+
+@pytest.mark.parametrize("variant", ["auto", "melded"])
+def test_later_calls_leave_a_captured_segmented_sort_its_queues(ctx, variant):
+    off = workloads.segment_offsets(8, 100)
+    n = int(off[-1])
+    work, od = _to_dev(workloads.keys_u32(8, n)), _to_dev(off)
+    meld.segmented_sort(work, od, variant=variant, ctx=ctx)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        meld.segmented_sort(work, od, variant=variant, ctx=ctx)
+    for seed, nseg in ((9, 0), (10, 3000), (11, 70_000)):
+        if nseg:
+            more = torch.arange(nseg + 1, dtype=torch.int32, device="cuda:0") * 3
+            kd = _to_dev(workloads.keys_u32(seed, 3 * nseg))
+            ref = (kd.view(-1, 3).cpu().numpy().view(np.uint32)).copy()
+            meld.segmented_sort(kd, more, variant=variant, ctx=ctx)
+            torch.cuda.synchronize()
+            assert np.array_equal(kd.cpu().numpy().view(np.uint32).reshape(-1, 3),
+                                  np.sort(ref, axis=1))
+            junk = torch.full((4 << 20,), -1, dtype=torch.int32, device="cuda:0")
+        keys = workloads.keys_u32(seed, n)
+        for _ in range(2):
+            work.copy_(_to_dev(keys))
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(work.cpu().numpy().view(np.uint32),
+                                  oracle.segmented_sort_u32(keys, off))
+        assert not nseg or bool((junk == -1).all())
+    meld.segmented_sort_check(0, ctx=ctx)
