@@ -459,6 +459,23 @@ uint32_t default_log_tile(bool pairs, uint32_t log_n) {
     return std::max(kMinLogRegsTile, std::min(t, max_log_tile(pairs)));
 }
 
+// The network's tile where MELD_AUTO has no decision of the tuner's: under capture and
+// without allocation. Those calls used to find the decision that an eager call had
+// timed, but most eager calls take another sort now and time nothing. So this is the
+// tile that the trials chose: the fastest of 2^10 .. 2^14 for a power of two, three
+// quarters of it and just over half, in microseconds against the rule above. Keys 2^12
+// 10.3 / 11.3, 2^13 16.3 / 17.6, 2^16 34.8 / 37.5, 2^17 43.2 / 50.7 (12 and 11); 2^18
+// 57.6 / 66.5, 2^20 103.7 / 113.0 (13 and 11, 12); 2^21 160 / 184 (13 and 12). Pairs 2^12 21.0 /
+// 21.5 and 3077 22.4 / 25.0 (12 and 11), 2^21 - 2^19 267 / 294 and 2^22 355 / 370 (13
+// and 12); 2^23 with 13 686 against 693, but 565 against 587 for 3 2^21; 2^24 1328 /
+// 1349, 2^25 2688 / 2767. The forms stay melded with lane exchanges, which the trials
+// chose at every size.
+uint32_t auto_log_tile(bool pairs, uint32_t log_n) {
+    if (!pairs) return log_n <= 17 ? 12 : log_n <= 21 ? 13 : 14;
+    if (log_n >= 13 && log_n <= 20) return default_log_tile(true, log_n);
+    return log_n <= 12 || log_n == 23 ? 12 : 13;
+}
+
 // Sizes (high bits first) of the streaming passes of d global steps: the
 // fewest passes of at most max_gather steps, as equal as possible (a gathered
 // pass of 8 pair steps has rows of only 128 bytes and runs slower than one of
@@ -701,9 +718,10 @@ meld_status sort_impl(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, size_t n
 }
 
 // The tile the context fixes (MELD_OPT_SORT_LOG_TILE), else the size rule.
-uint32_t plan_log_tile(const meld_ctx *ctx, bool pairs, uint32_t log_n) {
-    if (ctx->sort_log_tile != 0) return std::min(ctx->sort_log_tile, max_log_tile(pairs));
-    return default_log_tile(pairs, log_n);
+uint32_t plan_log_tile(const meld_ctx *ctx, bool pairs, uint32_t log_n, meld_variant v) {
+    if (ctx != nullptr && ctx->sort_log_tile != 0)
+        return std::min(ctx->sort_log_tile, max_log_tile(pairs));
+    return v == MELD_AUTO ? auto_log_tile(pairs, log_n) : default_log_tile(pairs, log_n);
 }
 
 // Lane exchanges unless the context asks for the LDS comparator network.
@@ -711,7 +729,7 @@ bool plan_xch(const meld_ctx *ctx) { return ctx->lane_exchange != 0; }
 
 SortPlan fixed_plan(const meld_ctx *ctx, bool pairs, size_t n, meld_variant v) {
     const bool m = use_melded(v);
-    return SortPlan{plan_log_tile(ctx, pairs, log2_ceil(n)), m, m, plan_xch(ctx)};
+    return SortPlan{plan_log_tile(ctx, pairs, log2_ceil(n), v), m, m, plan_xch(ctx)};
 }
 
 meld_status small_sort(uint32_t *keys, uint32_t *payload, size_t n, hipStream_t s) {
@@ -831,7 +849,7 @@ meld_status auto_sort_plan(meld_ctx *ctx, uint32_t *keys, uint32_t *payload, siz
     const uint32_t forced = ctx->sort_log_tile ? std::min(ctx->sort_log_tile, max_t) : 0;
     const std::string key = sort_tune_key(ctx, pairs, log_n);
     if (cached_sort_plan(ctx, pairs, log_n, out)) return MELD_OK;
-    *out = SortPlan{plan_log_tile(ctx, pairs, log_n), true, true, plan_xch(ctx)};
+    *out = SortPlan{plan_log_tile(ctx, pairs, log_n, MELD_AUTO), true, true, plan_xch(ctx)};
     if (capturing(s)) return MELD_OK;  // no timing inside a capture; untuned default
     // Candidate tiles: from one that leaves a few hundred tiles up to the
     // largest (a single tile when everything fits); the forced one alone.
@@ -1476,7 +1494,7 @@ meld_status meld_sort_plan_describe(meld_ctx *ctx, size_t n, int with_payload,
     const bool pairs = with_payload != 0;
     const uint32_t log_n = n <= 1 ? 0 : log2_ceil(n);
     const bool m = variant == MELD_AUTO || use_melded(variant);
-    SortPlan plan{default_log_tile(pairs, log_n), m, m, true};
+    SortPlan plan{plan_log_tile(nullptr, pairs, log_n, variant), m, m, true};
     bool tuned = false;
     const char *by = "network";
     if (ctx != nullptr) {
@@ -1485,7 +1503,7 @@ meld_status meld_sort_plan_describe(meld_ctx *ctx, size_t n, int with_payload,
             constexpr const char *kNames[] = {"network", "registers", "ranks", "radix"};
             by = kNames[(int)auto_sort_by(ctx, pairs, n, true)];
         }
-        plan.log_t = plan_log_tile(ctx, pairs, log_n);
+        plan.log_t = plan_log_tile(ctx, pairs, log_n, variant);
         plan.xch = plan_xch(ctx);
         if (variant == MELD_AUTO) tuned = cached_sort_plan(ctx, pairs, log_n, &plan);
     }
