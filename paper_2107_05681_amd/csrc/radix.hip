@@ -41,6 +41,11 @@ struct RadixArgs {
     uint32_t *ctl;     // mask of the word's passes that run
 };
 
+// A wave's 16-bit digit counts, which other lanes clear and add up two to a word
+// between barriers of the wave, which order no memory by themselves: a type that may
+// alias the words keeps the compiler from moving these accesses past those.
+typedef uint16_t __attribute__((may_alias)) Count16;
+
 __device__ __forceinline__ uint32_t digit_of(uint32_t x, uint32_t shift) {
     return (x >> shift) & (kDigits - 1);
 }
@@ -384,7 +389,7 @@ __global__ __launch_bounds__(NT) void radix_scatter_kernel(RadixArgs a) {
     uint32_t *wc32 = exch + TILE;  // [wave][digit]: 16-bit counts, two a word
     uint32_t *goff = wc32 + W * kDigits / 2;
     const uint32_t t = threadIdx.x, lane = t & 63, w = t / 64;
-    uint16_t *wc = reinterpret_cast<uint16_t *>(wc32) + w * kDigits;
+    Count16 *wc = reinterpret_cast<Count16 *>(wc32) + w * kDigits;
 
     uint32_t run;
     if (!SCANNED && a.pass == 0) {
@@ -467,7 +472,7 @@ __global__ __launch_bounds__(NT) void radix_scatter_kernel(RadixArgs a) {
             const uint32_t below = __builtin_amdgcn_mbcnt_hi(
                 (uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0));
             __builtin_amdgcn_wave_barrier();
-            wc[d] = (uint16_t)(old + __popcll(peers));  // the same value from every peer
+            wc[d] = (Count16)(old + __popcll(peers));  // the same value from every peer
             __builtin_amdgcn_wave_barrier();
             pos[i] = old + below;
             asm volatile("" : "+v"(pos[i]));
