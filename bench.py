@@ -317,7 +317,8 @@ def main():
         "data": "synthetic (seeded SplitMix64 keys, payload = index; workloads/)",
         "config": {
             "workload": "bitonic sort of 2^28 (u32 key, u32 payload = original index) pairs, "
-                        "keys uniform from seed 1, in place in HBM, MELD_AUTO",
+                        "keys uniform from seed 1, in place in HBM, the network with MELD_AUTO's "
+                        "tuned plan (auto_call: what MELD_AUTO itself runs)",
             "n": n, "seed": SEED, "variant": "auto",
             "log_tile": plan["log_tile"], "low_phases": plan["low"],
             "high_phases": plan["high"], "hbm_passes": plan["hbm_passes"],
@@ -622,6 +623,7 @@ def _bench_region(torch, np, meld, workloads, dev, args):
                 raise SystemExit(f"auto and {other} region differ at p={p}")
 
     launch_us = step_ms * 1e3 / len(PS)
+    form = _tuned_region_form(meld, st["trips"], sf["trips"])
     return {
         "workload": "two-sided loop region: 2^24 fp32 lanes x p in {0.1,0.5,0.9}, branch bit "
                     "Bernoulli(p) from hash(seed,i), each side 8-32 fma+gather steps into a "
@@ -629,16 +631,19 @@ def _bench_region(torch, np, meld, workloads, dev, args):
         "trips_true": st["trips"], "trips_false": sf["trips"],
         "step_ms": round(step_ms, 4), "G_lanes_s": round(len(PS) * N_LANES / step_ms / 1e6, 2),
         "roofline": {
-            "bound": "hbm", "kernel": "region_melded_kernel (MELD_AUTO step, one launch per p)",
+            "bound": "hbm",
+            "kernel": f"MELD_AUTO step, one launch per p (form at p = 0.5: {form})",
             "avg_launch_us": round(launch_us, 2),
             "achieved": round(REGION_COMPULSORY / (launch_us * 1e-6) / 1e9, 1),
             "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(REGION_COMPULSORY / (launch_us * 1e-6) / 1e9 / HBM_PEAK_GBS, 4),
-            "traffic": _measured_traffic("region_melded_traffic.json"),
+            "traffic": (_measured_traffic("region_melded_traffic.json") if form == "melded"
+                        else None),
             "alg_bytes_per_launch": int(REGION_COMPULSORY),
             "note": "compulsory bytes: x read, y written and the 64 MiB table read once "
-                    "(3 x 64 MiB); the gathers re-read table entries from L2 / MALL, so the "
-                    "kernel is bound by the vector-memory address path, not by HBM"},
+                    "(3 x 64 MiB); the gathers re-read table entries from L2 / MALL, so a lane "
+                    "per thread is bound by the vector-memory address path and four lanes by "
+                    "the L2, not by HBM"},
         "melded_vs_divergent": per_p,
         "same_index_sides": same_index,
         "trips_sweep_p0.5": trips_sweep,

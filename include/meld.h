@@ -14,8 +14,9 @@
  *                   operands become one access, and only unaligned work stays
  *                   under a branch (the "Unpredication" subsection).
  *   MELD_AUTO       the library picks per stage (measured divergence and the
- *                   tuned plan). meld_sort_u32 then also picks the algorithm:
- *                   the network for small arrays, radix passes above.
+ *                   tuned plan). Where only the order of the result counts it
+ *                   also picks the algorithm: one workgroup in registers, runs
+ *                   and ranks, radix passes or the network (see each call).
  *   MELD_MELDED_INPLACE  for the region: the melded form with the two sides'
  *                   gathers aligned too (one gather instruction per step,
  *                   address selected per lane). MELD_MELDED leaves those
@@ -78,7 +79,7 @@ typedef enum {
 int meld_version(void);
 
 /* Creates a context on HIP device `hip_device`. The context owns the
- * library's scratch memory (tail padding for non-power-of-two sorts, work
+ * library's scratch memory (second copies of the arrays of large sorts, work
  * queues, counters), which grows on demand and is freed by meld_destroy. */
 meld_status meld_create(int hip_device, meld_ctx **out);
 
@@ -442,10 +443,14 @@ meld_status meld_probe_segments(meld_ctx *ctx, const uint32_t *offsets, size_t n
  * trip counts and p in tenths). The first call of a class times the
  * candidates on the caller's stream — sorts on a scratch copy of the input
  * (tile size x divergent/melded per stage), the region on the caller's own
- * arrays (its three forms, and one with four lanes per thread) — runs the matching divergence probe, and keeps
- * the decision (see meld_tune_choose). Later calls reuse it. An entry's key also
- * names the candidates ("r", "q"), so that a file of a library with fewer of them
- * is read but its entries are timed anew. A stream that is being captured gets the untuned default (melded) without timing. */
+ * arrays (its three forms, and one with four lanes per thread) — runs the
+ * matching divergence probe, and keeps the decision (see meld_tune_choose).
+ * Later calls reuse it. An entry's key also names the candidates ("r", "q"), so
+ * that a file of a library with fewer of them is read but its entries are timed
+ * anew. A stream that is being captured gets the decision that the tuner holds
+ * (the segmented sort: none), else the untuned default, which is melded, without
+ * timing. Sorts, merge sorts and buckets that MELD_AUTO runs by another algorithm
+ * time nothing. */
 
 /* Loads decisions from the JSON file cache_path (if it exists and was
  * written on the same GPU architecture and HIP runtime) and saves every new

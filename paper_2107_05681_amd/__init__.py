@@ -214,8 +214,7 @@ def _u32_tensor(t, name):
 
 def sort(keys, payload=None, variant=AUTO, stream=None, ctx=None, noalloc=False):
     """In-place ascending bitonic sort of ``keys`` (u32 bits), moving ``payload`` along.
-    noalloc: through meld_sort_u32_noalloc (no device allocation; padding in the
-    library's fixed device scratch)."""
+    noalloc: through meld_sort_u32_noalloc (no device allocation, no scratch)."""
     _u32_tensor(keys, "keys")
     if payload is not None:
         _u32_tensor(payload, "payload")

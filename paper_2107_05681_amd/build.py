@@ -14,9 +14,10 @@ LIB = os.path.join(PKG, "libmeld.so")
 
 # Longest compiles first (the local tile sorts unroll every phase).
 SOURCES = ["bitonic_local_xch.hip", "bitonic_local_lds.hip", "bitonic.hip", "segsort.hip",
-           "segsort_auto.hip", "radix.hip", "bucket_sort.hip", "rank_sort.hip", "small_sort.hip", "region.hip", "region_variants.hip",
-           "region_quad.hip", "merge_wave.hip", "oddeven.hip",
-           "mergesort.hip", "probe.hip", "gen.hip", "meld.cpp", "tune.cpp", "serve.cpp"]
+           "segsort_auto.hip", "radix.hip", "bucket_sort.hip", "rank_sort.hip", "small_sort.hip",
+           "region.hip", "region_variants.hip", "region_quad.hip", "merge_wave.hip",
+           "oddeven.hip", "mergesort.hip", "probe.hip", "gen.hip", "meld.cpp", "tune.cpp",
+           "serve.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

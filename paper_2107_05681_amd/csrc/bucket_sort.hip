@@ -40,8 +40,10 @@ __device__ __forceinline__ void store_some(uint32_t *keys, uint32_t n, uint32_t 
 // arrays that are not aligned); the sorted tile goes through LDS to be stored
 // the same way. Keys past n are padding, which sorts behind every key.
 //
-// 2^26 keys in buckets of 2^13 take 210 us (the odd-even network with one LDS
-// access per key and step: 1070 us), 2^11: 155 us, 2^6: 85 us. VALU issue bounds
+// 2^26 keys in buckets of 2^13 take 212 us (passes of 310 less 98 for the copy of the
+// input; a kernel trace averages 260 over the first 13 calls, until the clock settles,
+// and ends at 228), the odd-even network with one LDS access per key and step 1070 us;
+// buckets of 2^11 155 us, 2^6: 85 us. VALU issue bounds
 // the large buckets (131 operations a key at 2^13: 215 us on 1024 SIMDs), the
 // transfer the small ones (537 MB).
 template <int LOG, bool VEC>

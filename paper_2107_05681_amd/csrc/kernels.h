@@ -121,7 +121,8 @@ constexpr uint32_t kMinGatherStepsPairs = 5;
 // Steps j = 2^(log_t-1) .. 1 of phase k = 2^m > 2^log_t on every tile, in
 // registers with LDS transposes (log_t in 8..14). At most step_limit steps run
 // (negative: all).
-hipError_t launch_bitonic_merge(const SortArray &a, uint32_t log_t, uint32_t m, int32_t step_limit, int io_mode, hipStream_t stream);
+hipError_t launch_bitonic_merge(const SortArray &a, uint32_t log_t, uint32_t m, int32_t step_limit,
+                                int io_mode, hipStream_t stream);
 
 // The same for keys alone and every step, 32 per lane (merge_wave.hip; log_t in
 // kMergeWaveMinLog..14).
@@ -166,7 +167,8 @@ hipError_t launch_small_sort(uint32_t *keys, uint32_t *payload, uint32_t n, hipS
 // Up to kRankSortMin keys one workgroup is faster.
 constexpr uint32_t kRankSortMin = 1u << 12, kRankSortMax = 1u << 17;
 constexpr uint32_t kRankPairsMin = 1u << 11, kRankPairsMax = 1u << 16;
-constexpr uint32_t kRankScratchWords = kRankSortMax + kRankSortMax / 8;  // pairs: 2^16 of twice the size
+// Pairs: half as many of twice the size.
+constexpr uint32_t kRankScratchWords = kRankSortMax + kRankSortMax / 8;
 hipError_t launch_rank_sort(uint32_t *keys, uint32_t *payload, uint32_t n, uint32_t *scratch,
                             hipStream_t stream);
 

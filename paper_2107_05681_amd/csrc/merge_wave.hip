@@ -9,7 +9,7 @@
 // steps again, bits 5 and 4 trade places with a register bit, bits 3 to 0 are DPP
 // medians (wave_network.h), and the keys are stored lane-linear as they stand. With
 // 16 keys per lane a tile of 2^14 moves through LDS four times (bitonic.hip): 10^7
-// keys, one tail: 23.4 us, 16.7 us so (a copy of the 40 MB takes 12.9 us).
+// keys, one tail: 23.4 us, 16.5 us so, 17.7 over the first calls (a copy of the 40 MB takes 12.9 us).
 #include "kernels.h"
 #include "wave_network.h"
 

@@ -15,7 +15,10 @@
 //
 // 2^23 lanes, 8 to 26 trips a lane, a 2^23-entry table: 184 us with a lane per
 // thread, 81 us so; three ways of 10, 10 and 28 trips on 2^24 lanes: 189 and 172 us;
-// two sides of 10 trips on 2^24 lanes: 102 and 97 us. What bounds it now is the L2:
+// two sides of 10 trips on 2^24 lanes: 102 and 97 us. The tuner times the forms on the
+// same arrays again and again; within its 2 % it may take this one where a lane per
+// thread is as fast then (8 and 32 trips: 112 us against 110), and with inputs that
+// change it is the faster (138 against 154). What bounds it now is the L2:
 // 1.5 GB of the last call's entries come from it in 70 us when the table is there.
 #include <algorithm>
 #include <type_traits>

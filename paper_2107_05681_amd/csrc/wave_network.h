@@ -1,6 +1,7 @@
-// Bitonic network of u32 keys held 32 per lane, every comparator ascending.
+// Bitonic network of u32 keys, or u64 (key, payload) composites, held 32, 16 or 8 per
+// lane, every comparator ascending.
 //
-// A wave holds 2^11 keys: element bits 0 .. 4 are the register index, bits
+// With 32 per lane a wave holds 2^11 keys: element bits 0 .. 4 are the register index, bits
 // 5 .. 10 the lane; above that, bits 11 .. 13 are the wave of a workgroup that
 // sorts up to 2^14 keys. MELD_AUTO uses it where only the sorted order counts,
 // so there is one form, and two things that the paper's forms cannot do:
